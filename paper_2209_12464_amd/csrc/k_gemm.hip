@@ -1,5 +1,7 @@
 // Dense products with A on the matrix cores: Y = A X (NN) and Y = A^T X (TN),
-// the sketch, power-step and projection products of Algorithms 1 and 2.
+// the sketch, power-step and projection products of Algorithms 1 and 2.  The
+// kernel here is the float64 one (float32: k_gemm32.hip); the launch of a
+// product and the split-K reduction serve both.
 //
 // The output is tall and skinny (d columns), so one workgroup owns a BM-row
 // slab of Y and all of its columns up to 256 (wider outputs take equal
@@ -9,14 +11,10 @@
 // Workgroup ids are remapped so that an XCD works on a contiguous range of
 // (split, slab) pairs: the X chunk of a split then stays in that XCD's L2.
 //
-// Tiles: 8 waves as 4 (rows) x 2 (columns); each wave owns 16 MB rows and
-// half of the BN = 32 * NBW columns, i.e. MB x NBW blocks of 16 x 16
-// accumulated with the 16x16x4 MFMA (float or double).  MB = 2 (128-row
-// slabs, two workgroups per CU) is the default shape; MB = 4 (256-row slabs,
-// float only, one workgroup per CU, fewer LDS operand reads per MFMA) is the
-// alternative the autotuner may pick per product shape.  BK = 16 along the
-// reduction.  A and X tiles are staged through LDS, double buffered with
-// register prefetch, one barrier per K step.
+// Tiles: 8 waves as 4 (rows) x 2 (columns); each wave owns 32 rows and half of
+// the BN = 32 * NBW columns, i.e. 2 x NBW blocks of 16 x 16 accumulated with
+// the 16x16x4 MFMA.  BK = 16 along the reduction.  A and X tiles are staged
+// through LDS, double buffered with register prefetch, one barrier per K step.
 #include "common.h"
 #include "grouped.h"
 #include "kernels.h"
@@ -29,27 +27,27 @@ constexpr int kGemmThreads = 512;
 constexpr int kBK = 16;
 
 // One workgroup's share: tile `logical` = split * mtiles + slab.
-template <typename T, int NBW, bool TRANS, bool AVEC, bool BVEC, int MB>
+template <int NBW, bool TRANS, bool AVEC, bool BVEC>
 __device__ __attribute__((always_inline)) inline void gemm_body(
-    const T* __restrict__ A, int64_t lda, const T* __restrict__ B, int64_t ldb,
-    T* __restrict__ C, int64_t ldc, int64_t cslice, int M, int N, int K, int kchunk, int mtiles,
+    const double* __restrict__ A, int64_t lda, const double* __restrict__ B, int64_t ldb,
+    double* __restrict__ C, int64_t ldc, int64_t cslice, int M, int N, int K, int kchunk, int mtiles,
     int nst, int logical) {
-  typedef Mfma<T> MF;
+  typedef Mfma<double> MF;
+  constexpr int MB = 2;                    // 16-row blocks per wave
   constexpr int BM = 64 * MB;              // 4 row groups x 16 MB rows
   constexpr int BN = 32 * NBW;             // 2 column halves x NBW blocks of 16
-  constexpr int VEC = 16 / sizeof(T);
+  constexpr int VEC = 2;
   // LDS row strides of 16 (mod 32) words: the two k-rows an operand read
   // touches in one 32-lane half then fall in disjoint banks
   constexpr int AS = BM + 16;              // A tile, k-major
   constexpr int BS = BN + 16;              // X tile
-  constexpr int A_ELEMS = BM * kBK / kGemmThreads;   // 2 MB per thread
-  static_assert(MB == 2 || MB == 4, "row tile of 128 or 256 rows");
+  constexpr int A_ELEMS = BM * kBK / kGemmThreads;   // 4 per thread
   constexpr int A_VECS = A_ELEMS / VEC;
   constexpr int B_VECS = (kBK * BN / VEC + kGemmThreads - 1) / kGemmThreads;
   constexpr int B_ELEMS = BVEC ? B_VECS * VEC : (kBK * BN + kGemmThreads - 1) / kGemmThreads;
 
-  __shared__ __attribute__((aligned(16))) T As[2][kBK][AS];
-  __shared__ __attribute__((aligned(16))) T Bs[2][kBK][BS];
+  __shared__ __attribute__((aligned(16))) double As[2][kBK][AS];
+  __shared__ __attribute__((aligned(16))) double Bs[2][kBK][BS];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -61,8 +59,8 @@ __device__ __attribute__((always_inline)) inline void gemm_body(
   const int kbeg = split * kchunk;
   const int kend = min(K, kbeg + kchunk);
 
-  T areg[A_ELEMS];
-  T breg[B_ELEMS];
+  double areg[A_ELEMS];
+  double breg[B_ELEMS];
 
   auto load_tile = [&](int k0) {
     if constexpr (!TRANS) {
@@ -74,20 +72,14 @@ __device__ __attribute__((always_inline)) inline void gemm_body(
           const int r = idx / (kBK / VEC), kv = idx % (kBK / VEC);
           const int gr = m0 + r, gk = k0 + kv * VEC;
           if (gr < M && gk + VEC <= kend) {
-            const T* p = A + (int64_t)gr * lda + gk;
-            if constexpr (VEC == 4) {
-              const floatx4 x = *reinterpret_cast<const floatx4*>(p);
-#pragma unroll
-              for (int e = 0; e < VEC; ++e) areg[v * VEC + e] = x[e];
-            } else {
-              const double2 x = *reinterpret_cast<const double2*>(p);
-              areg[v * VEC + 0] = x.x;
-              areg[v * VEC + 1] = x.y;
-            }
+            const double* p = A + (int64_t)gr * lda + gk;
+            const double2 x = *reinterpret_cast<const double2*>(p);
+            areg[v * VEC + 0] = x.x;
+            areg[v * VEC + 1] = x.y;
           } else {
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
-              areg[v * VEC + e] = (gr < M && gk + e < kend) ? A[(int64_t)gr * lda + gk + e] : (T)0;
+              areg[v * VEC + e] = (gr < M && gk + e < kend) ? A[(int64_t)gr * lda + gk + e] : 0.0;
           }
         }
       } else {
@@ -96,7 +88,7 @@ __device__ __attribute__((always_inline)) inline void gemm_body(
           const int idx = tid + kGemmThreads * i;
           const int r = idx / kBK, kk = idx % kBK;
           const int gr = m0 + r, gk = k0 + kk;
-          areg[i] = (gr < M && gk < kend) ? A[(int64_t)gr * lda + gk] : (T)0;
+          areg[i] = (gr < M && gk < kend) ? A[(int64_t)gr * lda + gk] : 0.0;
         }
       }
     } else {
@@ -108,20 +100,14 @@ __device__ __attribute__((always_inline)) inline void gemm_body(
           const int kk = idx / (BM / VEC), rv = idx % (BM / VEC);
           const int gk = k0 + kk, gc = m0 + rv * VEC;
           if (gk < kend && gc + VEC <= M) {
-            const T* p = A + (int64_t)gk * lda + gc;
-            if constexpr (VEC == 4) {
-              const floatx4 x = *reinterpret_cast<const floatx4*>(p);
-#pragma unroll
-              for (int e = 0; e < VEC; ++e) areg[v * VEC + e] = x[e];
-            } else {
-              const double2 x = *reinterpret_cast<const double2*>(p);
-              areg[v * VEC + 0] = x.x;
-              areg[v * VEC + 1] = x.y;
-            }
+            const double* p = A + (int64_t)gk * lda + gc;
+            const double2 x = *reinterpret_cast<const double2*>(p);
+            areg[v * VEC + 0] = x.x;
+            areg[v * VEC + 1] = x.y;
           } else {
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
-              areg[v * VEC + e] = (gk < kend && gc + e < M) ? A[(int64_t)gk * lda + gc + e] : (T)0;
+              areg[v * VEC + e] = (gk < kend && gc + e < M) ? A[(int64_t)gk * lda + gc + e] : 0.0;
           }
         }
       } else {
@@ -130,7 +116,7 @@ __device__ __attribute__((always_inline)) inline void gemm_body(
           const int idx = tid + kGemmThreads * i;
           const int kk = idx / BM, r = idx % BM;
           const int gk = k0 + kk, gc = m0 + r;
-          areg[i] = (gk < kend && gc < M) ? A[(int64_t)gk * lda + gc] : (T)0;
+          areg[i] = (gk < kend && gc < M) ? A[(int64_t)gk * lda + gc] : 0.0;
         }
       }
     }
@@ -142,17 +128,10 @@ __device__ __attribute__((always_inline)) inline void gemm_body(
         const int kk = idx / (BN / VEC), nv = idx % (BN / VEC);
         const int gk = k0 + kk;
         const bool ok = idx < kBK * BN / VEC && gk < kend;
-        if constexpr (VEC == 4) {
-          floatx4 x = {0.f, 0.f, 0.f, 0.f};
-          if (ok) x = *reinterpret_cast<const floatx4*>(B + (int64_t)gk * ldb + nv * VEC);
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) breg[v * VEC + e] = x[e];
-        } else {
-          double2 x = {0.0, 0.0};
-          if (ok) x = *reinterpret_cast<const double2*>(B + (int64_t)gk * ldb + nv * VEC);
-          breg[v * VEC + 0] = x.x;
-          breg[v * VEC + 1] = x.y;
-        }
+        double2 x = {0.0, 0.0};
+        if (ok) x = *reinterpret_cast<const double2*>(B + (int64_t)gk * ldb + nv * VEC);
+        breg[v * VEC + 0] = x.x;
+        breg[v * VEC + 1] = x.y;
       }
     } else {
 #pragma unroll
@@ -160,7 +139,7 @@ __device__ __attribute__((always_inline)) inline void gemm_body(
         const int idx = tid + kGemmThreads * i;
         const int kk = idx / BN, n = idx % BN;
         const int gk = k0 + kk;
-        breg[i] = (idx < kBK * BN && gk < kend && n < N) ? B[(int64_t)gk * ldb + n] : (T)0;
+        breg[i] = (idx < kBK * BN && gk < kend && n < N) ? B[(int64_t)gk * ldb + n] : 0.0;
       }
     }
   };
@@ -238,7 +217,7 @@ __device__ __attribute__((always_inline)) inline void gemm_body(
       // The operands of step ks + 1 are read from LDS while the MFMAs of
       // step ks issue, and the wave's priority is raised for the MFMA loop
       // so that the co-resident workgroup's loads and stores fill its gaps.
-      T aa[2][MB], bb[2][NBW];
+      double aa[2][MB], bb[2][NBW];
       {
         const int kr = (lane >> 4);
 #pragma unroll
@@ -270,7 +249,7 @@ __device__ __attribute__((always_inline)) inline void gemm_body(
   }
 
   // ---- epilogue: write the slab (or this split's partial slab) ----
-  T* Cs = C + (int64_t)split * cslice;
+  double* Cs = C + (int64_t)split * cslice;
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -284,12 +263,12 @@ __device__ __attribute__((always_inline)) inline void gemm_body(
     }
 }
 
-template <typename T, int NBW, bool TRANS, bool AVEC, bool BVEC, int MB>
+template <int NBW, bool TRANS, bool AVEC, bool BVEC>
 __global__ __launch_bounds__(kGemmThreads) void gemm_kernel(
-    const T* __restrict__ A, int64_t lda, const T* __restrict__ B, int64_t ldb,
-    T* __restrict__ C, int64_t ldc, int64_t cslice, int M, int N, int K, int kchunk, int mtiles,
+    const double* __restrict__ A, int64_t lda, const double* __restrict__ B, int64_t ldb,
+    double* __restrict__ C, int64_t ldc, int64_t cslice, int M, int N, int K, int kchunk, int mtiles,
     int nst) {
-  gemm_body<T, NBW, TRANS, AVEC, BVEC, MB>(A, lda, B, ldb, C, ldc, cslice, M, N, K, kchunk, mtiles, nst,
+  gemm_body<NBW, TRANS, AVEC, BVEC>(A, lda, B, ldb, C, ldc, cslice, M, N, K, kchunk, mtiles, nst,
                                            xcd_remap(blockIdx.x, gridDim.x));
 }
 
@@ -301,18 +280,18 @@ struct GemmRecArgs {
   int M, N, K, kchunk, mtiles, nst;
 };
 
-template <typename T, int NBW, bool TRANS, bool AVEC, bool BVEC, int MB>
+template <int NBW, bool TRANS, bool AVEC, bool BVEC>
 __global__ __launch_bounds__(kGemmThreads) void gemm_grouped(const GemmRecArgs* __restrict__ a,
                                                              const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const GemmRecArgs g = a[p];
-  gemm_body<T, NBW, TRANS, AVEC, BVEC, MB>((const T*)g.A, g.lda, (const T*)g.B, g.ldb, (T*)g.C, g.ldc, g.cslice,
+  gemm_body<NBW, TRANS, AVEC, BVEC>((const double*)g.A, g.lda, (const double*)g.B, g.ldb, (double*)g.C, g.ldc, g.cslice,
                                            g.M, g.N, g.K, g.kchunk, g.mtiles, g.nst, (int)blockIdx.x - start[p]);
 }
 
-template <typename T, int NBW, bool TRANS, bool AVEC, bool BVEC, int MB>
+template <int NBW, bool TRANS, bool AVEC, bool BVEC>
 void gemm_grouped_launch(const void* args, const int* start, int count, unsigned blocks, hipStream_t s) {
-  hipLaunchKernelGGL((gemm_grouped<T, NBW, TRANS, AVEC, BVEC, MB>), dim3(blocks), dim3(kGemmThreads), 0, s,
+  hipLaunchKernelGGL((gemm_grouped<NBW, TRANS, AVEC, BVEC>), dim3(blocks), dim3(kGemmThreads), 0, s,
                      (const GemmRecArgs*)args, start, count);
 }
 
@@ -410,16 +389,16 @@ static void splitk_dispatch(const T* P, int nsplit, int M, int nst, T* Y, int64_
   }
 }
 
-template <typename T, int NBW, bool TRANS, int MB>
-static void launch_nb(const GemmArgs<T>& g, hipStream_t s, int grid, T* C, int64_t ldc,
-                      int64_t cslice, int nst) {
+template <int NBW, bool TRANS>
+static void launch_nb(const GemmArgs<double>& g, hipStream_t s, int grid, double* C, int64_t ldc, int64_t cslice,
+                      int nst) {
 #define RQLP_GEMM_LAUNCH(AV, BV)                                                                                 \
   do {                                                                                                             \
-    if (!record_launch(&gemm_grouped_launch<T, NBW, TRANS, AV, BV, MB>,                                            \
+    if (!record_launch(&gemm_grouped_launch<NBW, TRANS, AV, BV>,                                                   \
                        GemmRecArgs{g.A, g.B, C, g.lda, g.ldb, ldc, cslice, g.M, g.N, g.K, g.kchunk, g.mtiles, nst}, \
                        (unsigned)grid))                                                                            \
-      hipLaunchKernelGGL((gemm_kernel<T, NBW, TRANS, AV, BV, MB>), dim3(grid), dim3(kGemmThreads), 0, s, g.A,       \
-                         g.lda, g.B, g.ldb, C, ldc, cslice, g.M, g.N, g.K, g.kchunk, g.mtiles, nst);               \
+      hipLaunchKernelGGL((gemm_kernel<NBW, TRANS, AV, BV>), dim3(grid), dim3(kGemmThreads), 0, s, g.A, g.lda, g.B,  \
+                         g.ldb, C, ldc, cslice, g.M, g.N, g.K, g.kchunk, g.mtiles, nst);                           \
   } while (0)
   if (g.avec && g.bvec) RQLP_GEMM_LAUNCH(true, true);
   else if (g.avec) RQLP_GEMM_LAUNCH(true, false);
@@ -428,31 +407,30 @@ static void launch_nb(const GemmArgs<T>& g, hipStream_t s, int grid, T* C, int64
 #undef RQLP_GEMM_LAUNCH
 }
 
-template <typename T, bool TRANS, int MB>
-static void dispatch_nb_mb(const GemmArgs<T>& g, hipStream_t s, int grid, T* C, int64_t ldc,
-                           int64_t cslice, int nst) {
-  switch (gemm_block_cols<T>(g.N) / 32) {
-    case 1: launch_nb<T, 1, TRANS, MB>(g, s, grid, C, ldc, cslice, nst); break;
-    case 2: launch_nb<T, 2, TRANS, MB>(g, s, grid, C, ldc, cslice, nst); break;
-    case 3: launch_nb<T, 3, TRANS, MB>(g, s, grid, C, ldc, cslice, nst); break;
-    case 4: launch_nb<T, 4, TRANS, MB>(g, s, grid, C, ldc, cslice, nst); break;
-    case 5: launch_nb<T, 5, TRANS, MB>(g, s, grid, C, ldc, cslice, nst); break;
-    case 6: launch_nb<T, 6, TRANS, MB>(g, s, grid, C, ldc, cslice, nst); break;
-    case 7: launch_nb<T, 7, TRANS, MB>(g, s, grid, C, ldc, cslice, nst); break;
-    default: launch_nb<T, 8, TRANS, MB>(g, s, grid, C, ldc, cslice, nst); break;
+template <bool TRANS>
+static void dispatch_nb(const GemmArgs<double>& g, hipStream_t s, int grid, double* C, int64_t ldc, int64_t cslice,
+                        int nst) {
+  switch (gemm_block_cols<double>(g.N) / 32) {
+    case 1: launch_nb<1, TRANS>(g, s, grid, C, ldc, cslice, nst); break;
+    case 2: launch_nb<2, TRANS>(g, s, grid, C, ldc, cslice, nst); break;
+    case 3: launch_nb<3, TRANS>(g, s, grid, C, ldc, cslice, nst); break;
+    case 4: launch_nb<4, TRANS>(g, s, grid, C, ldc, cslice, nst); break;
+    case 5: launch_nb<5, TRANS>(g, s, grid, C, ldc, cslice, nst); break;
+    case 6: launch_nb<6, TRANS>(g, s, grid, C, ldc, cslice, nst); break;
+    case 7: launch_nb<7, TRANS>(g, s, grid, C, ldc, cslice, nst); break;
+    default: launch_nb<8, TRANS>(g, s, grid, C, ldc, cslice, nst); break;
   }
 }
 
-template <typename T, bool TRANS>
-static void dispatch_nb(const GemmArgs<T>& g, hipStream_t s, int grid, T* C, int64_t ldc,
-                        int64_t cslice, int nst) {
-  if constexpr (sizeof(T) == 4) {
-    if (g.mb == 4) {
-      dispatch_nb_mb<T, TRANS, 4>(g, s, grid, C, ldc, cslice, nst);
-      return;
-    }
-  }
-  dispatch_nb_mb<T, TRANS, 2>(g, s, grid, C, ldc, cslice, nst);
+// The main kernel of one column pass (from column c0).
+static void launch_pass(const GemmArgs<double>& g, int, int grid, double* C, int64_t ldc, int64_t cslice, int nst,
+                        hipStream_t s) {
+  if (g.trans) dispatch_nb<true>(g, s, grid, C, ldc, cslice, nst);
+  else dispatch_nb<false>(g, s, grid, C, ldc, cslice, nst);
+}
+static void launch_pass(const GemmArgs<float>& g, int c0, int grid, float* C, int64_t ldc, int64_t cslice, int nst,
+                        hipStream_t s) {
+  launch_gemm32_tiles(g, c0, grid, C, ldc, cslice, nst, s);
 }
 
 template <typename T>
@@ -467,7 +445,7 @@ template int gemm_block_cols<double>(int);
 
 // Widest column tile of one pass; wider outputs are cut into equal passes
 // of at most this many columns (A is then streamed once per pass).
-constexpr int kGemmMaxCols = 256;
+template <typename T> constexpr int kGemmMaxCols = sizeof(T) == 4 ? 288 : 256;
 
 // Launch the main kernel (into C directly when nsplit == 1, else into the
 // partial buffer P) once per column pass and, for nsplit > 1, the ordered
@@ -477,24 +455,19 @@ hipError_t launch_gemm(GemmArgs<T> g, T* Y, int64_t ldy, int nst, T* P, hipStrea
                        hipEvent_t ev0, hipEvent_t ev1) {
   if (g.M <= 0 || nst <= 0) return hipSuccess;
   const int grid = g.mtiles * g.nsplit;
-  const int npass = (int)ceil_div(round_up(g.N, 32), kGemmMaxCols);
+  const int npass = (int)ceil_div(round_up(g.N, 32), kGemmMaxCols<T>);
   const int cw = (int)round_up(ceil_div(g.N, npass), 32);
   if (ev0) (void)hipEventRecord(ev0, s);
+  if constexpr (sizeof(T) == 4)
+    if (g.xsplit) launch_xsplit(g, cw, s);
   for (int c0 = 0; c0 < g.N; c0 += cw) {
     GemmArgs<T> gc = g;
     gc.B = g.B + c0;
     gc.N = std::min(cw, g.N - c0);
     // the last pass also writes the zero columns [N, nst)
     const int nst_c = (c0 + cw >= g.N) ? nst - c0 : cw;
-    if (g.nsplit == 1) {
-      if (g.trans) dispatch_nb<T, true>(gc, s, grid, Y + c0, ldy, 0, nst_c);
-      else dispatch_nb<T, false>(gc, s, grid, Y + c0, ldy, 0, nst_c);
-    } else {
-      const int64_t ldp = nst;
-      const int64_t pslice = (int64_t)g.M * ldp;
-      if (g.trans) dispatch_nb<T, true>(gc, s, grid, P + c0, ldp, pslice, nst_c);
-      else dispatch_nb<T, false>(gc, s, grid, P + c0, ldp, pslice, nst_c);
-    }
+    if (g.nsplit == 1) launch_pass(gc, c0, grid, Y + c0, ldy, 0, nst_c, s);
+    else launch_pass(gc, c0, grid, P + c0, (int64_t)nst, (int64_t)g.M * nst, nst_c, s);
   }
   if (g.nsplit > 1) splitk_dispatch<T>(P, g.nsplit, g.M, nst, Y, ldy, s);
   // the timed interval covers the product and its split-K reduction
