@@ -331,7 +331,8 @@ __global__ __launch_bounds__(kSvThreads) void svd_sweeps_kernel(double* __restri
 }
 
 // sigma_j, the sign of each pair and the descending order (one workgroup):
-// sig[o], src[o] (the column that goes to place o) and sgn[o].
+// sig[o], src[o] (the column that goes to place o) and sgn[o].  Columns that are
+// not a number come last, so that src is a permutation whatever the input holds.
 __global__ __launch_bounds__(1024) void svd_order_kernel(const double* __restrict__ XV, int d, int dp, const int32_t* __restrict__ flags,
                                                          int nflags, double* __restrict__ sig_out,
                                                          int32_t* __restrict__ src, double* __restrict__ sgn_out,
@@ -359,7 +360,7 @@ __global__ __launch_bounds__(1024) void svd_order_kernel(const double* __restric
     ss = __shfl(ss, 0);
     bi = __shfl(bi, 0);
     if (lane == 0) {
-      sig[j] = sqrt(ss);
+      sig[j] = ss == ss ? sqrt(ss) : -1.0;  // (-1: not a number)
       sgn[j] = X[dp + bi] < 0.0 ? -1.0 : 1.0;
     }
   }
@@ -368,7 +369,7 @@ __global__ __launch_bounds__(1024) void svd_order_kernel(const double* __restric
     const double sj = sig[j];
     int rank = 0;
     for (int i = 0; i < d; ++i) rank += (sig[i] > sj) || (sig[i] == sj && i < j);
-    sig_out[rank] = sj;
+    sig_out[rank] = sj < 0.0 ? __builtin_nan("") : sj;
     src[rank] = j;
     sgn_out[rank] = sgn[j];
   }

@@ -150,3 +150,23 @@ def test_decompose_svd_bf16_is_its_qlv_form(gpu_lib):
     assert np.linalg.norm(U @ np.diag(S) @ W.T - ref) / np.linalg.norm(ref) <= 1e-5
     assert np.all(np.diff(S) <= 0)
     assert np.abs(U.T @ U - np.eye(k + p)).max() <= 1e-5
+
+
+@pytest.mark.parametrize("d", [7, 33, 50])
+def test_svd_small_not_a_number(gpu_lib, d):
+    """Columns that hold a NaN or an infinity take no part in the rotations:
+    NaN singular values come last, in places of their own, and the other
+    columns give the singular values of the matrix without them."""
+    announce("svd_small not a number", d)
+    M = _lower(d, d + 1)
+    bad = [1, d // 2, d - 1]
+    clean = M.copy()
+    clean[:, bad] = 0.0
+    M[d // 2, bad[1]] = np.nan
+    M[0, bad[0]] = np.nan
+    M[d - 1, bad[2]] = np.inf
+    _, Sg, Vg = (to_np(x) for x in gpu_lib.svd_small(to_dev(M)))
+    _, So, _ = svd_small_oracle(clean)
+    assert Sg[0] == np.inf and np.isnan(Sg[-2:]).all()
+    assert np.abs(Sg[1:-2] - So[:-3]).max() <= 1e-13 * So[0] * np.sqrt(d)
+    assert np.abs(Vg.T @ Vg - np.eye(d)).max() <= 1e-13 * d
