@@ -53,6 +53,37 @@ def test_svd_small_matches_oracle(gpu_lib, d, dtype):
     _vectors_close(Vg, Vo, So, tol * 10)
 
 
+@pytest.mark.parametrize("d", [15, 16, 17, 33, 48, 49, 512, 528])
+@pytest.mark.parametrize("scale", [1.0, 1e70, 1e-70])
+def test_svd_small_block_edges(gpu_lib, d, scale):
+    """One, two and three blocks of 16 columns, an odd number of them (one
+    block meets none), and both layouts of the widest; scales whose squared
+    inner products leave the range in which angles are taken unscaled.  The
+    bounds are test_svd_small_matches_oracle's."""
+    announce("svd_small block edges", d, scale)
+    M = _lower(d, d) * scale
+    Ug, Sg, Vg = (to_np(x) / s for x, s in zip(gpu_lib.svd_small(to_dev(M)), (1.0, scale, 1.0)))
+    So = np.linalg.svd(M / scale, compute_uv=False)
+    tol = 1e-13
+    assert np.abs(Sg - So).max() <= tol * So[0] * np.sqrt(d)
+    assert np.abs(Ug @ np.diag(Sg) @ Vg.T - M / scale).max() <= tol * So[0] * d
+    assert np.abs(Vg.T @ Vg - np.eye(d)).max() <= tol * d
+    assert np.abs(Ug.T @ Ug - np.eye(d)).max() <= tol * d
+
+
+@pytest.mark.parametrize("d", [15, 16, 40])
+@pytest.mark.parametrize("value", [1.0, 0.1])
+def test_svd_small_rank_one(gpu_lib, d, value):
+    """Equal columns: after their rotations the squared norms that remain are
+    rounding errors of either sign and the inner products exact zeros."""
+    announce("svd_small rank one", d, value)
+    Ug, Sg, Vg = (to_np(x) for x in gpu_lib.svd_small(to_dev(np.full((d, d), value))))
+    tol = 1e-13
+    assert abs(Sg[0] - value * d) <= tol * value * d and Sg[1:].max() <= tol * value * d
+    assert np.abs(Ug @ np.diag(Sg) @ Vg.T - value).max() <= tol * value * d
+    assert np.abs(Vg.T @ Vg - np.eye(d)).max() <= tol * d
+
+
 def test_svd_small_special_cases(gpu_lib):
     """A diagonal matrix needs no rotation: the result is the oracle's signed
     permutation exactly; a zero column gives a zero singular value and a zero
