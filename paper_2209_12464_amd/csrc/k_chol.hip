@@ -2,17 +2,25 @@
 // middle step of each CholeskyQR pass (orth() and qr() of the paper,
 // computed as an unpivoted QR with a positive diagonal in R).
 //
-// For d <= 256, one workgroup of 8 waves, right-looking over 16-column blocks k.  The
-// lower triangle of G is cut into 16 x 16 tiles held in registers (MFMA
-// 16x16x4 accumulator layout: lane l holds rows l/16 + 4 s, column l % 16),
-// dealt round-robin to the waves.  Per block column k:
-//   A. the owner of tile (k,k) factors it in four steps of 4 pivots: a
-//      4 x 4 factorization on wave-uniform scalars, then MFMAs for the
-//      panel, the rank-4 trailing update and the running inverse of the
-//      16 x 16 factor;
-//   B. owners of tiles (i,k), i > k, form L_ik = G_ik L_kk^-T (4 MFMAs) and
-//      publish them in an LDS panel;
-//   C. owners of tiles (i,j), k < j <= i, update G_ij -= L_ik L_jk^T (MFMA).
+// For d <= 256, one workgroup of 16 waves, right-looking over 16-row blocks k of the
+// upper triangle.  The 16 x 16 tiles of G on and above the diagonal are held in
+// registers (MFMA 16x16x4 accumulator layout: lane l holds rows l/16 + 4 s, column
+// l % 16) by 12 waves, dealt to them row by row.  The other 4 waves, one a SIMD,
+// eliminate a block row: a lane has one column of it and all 16 rows, and each row
+// of 16 lanes a copy of the diagonal tile, so that a pivot's multipliers come from
+// the neighbour lanes and diagonal tile, panel and L_kk^-1 (the columns of the
+// identity) take their steps together, without MFMA or LDS in between.  Per k:
+//   A. the 4 waves eliminate block row k (in LDS) and put it back, while the 12
+//      do the rest of step k - 1, G_ij -= R_ti^T R_tj for t = k - 1 and i > k (MFMA),
+//      and store block row k - 1 of R;
+//   B. the 12 bring row k + 1 up to date with row k and put it in LDS.
+// What bounds it is the chain of A and B: about 3500 + 1500 cycles a step at 2.1
+// GHz, of which the 16 pivots' row operations are 1000 (240 FMAs of 4 cycles), and
+// with many tiles the float64 MFMAs of A (64 cycles each, 4 a tile, in the same
+// pipes as the elimination).  Before, the wave that owned the diagonal tile took it
+// in blocks of 4 pivots on wave-uniform scalars and MFMAs (5400 cycles), and panel
+// and update followed.  This kernel before and after (traced): d = 64
+// 15.6 -> 12.0 us, 110 30.5 -> 23.6, 176 51 -> 35, 192 59 -> 41, 210 75 -> 55.
 // Columns whose pivot is <= tol * (their original squared norm) are marked
 // dependent: their L column is zero, their R diagonal is 1 (so R stays
 // invertible for the solve) and the caller replaces the matching columns of
@@ -29,111 +37,149 @@
 #include "kernels.h"
 
 #include <algorithm>
+#include <utility>
 
 namespace rqlp {
 
-__device__ inline double bcast(double x, int lane) {
-  // value of x in lane `lane` (wave-uniform index), as a scalar broadcast
-  const int lo = __builtin_amdgcn_readlane(__double2loint(x), lane);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), lane);
-  return __hiloint2double(hi, lo);
+constexpr int kChE = 4;                    // waves that eliminate (one per SIMD)
+constexpr int kChU = 12;                   // waves that hold the tiles
+constexpr int kChWaves = kChE + kChU;
+constexpr int kChThreads = kChWaves * kWave;
+
+__device__ inline void tile_of(int t, int T, int& i, int& j) {
+  // upper triangle of T x T tiles, row by row: t = i T - i (i - 1) / 2 + j - i
+  i = 0;
+  while (t >= T - i) t -= T - i++;
+  j = i + t;
 }
 
-__device__ inline void tile_of(int t, int& i, int& j) {
-  // t = i (i + 1) / 2 + j, 0 <= j <= i
-  int ii = (int)((sqrtf(8.0f * t + 1.0f) - 1.0f) * 0.5f);
-  while ((ii + 1) * (ii + 2) / 2 <= t) ++ii;
-  while (ii * (ii + 1) / 2 > t) --ii;
-  i = ii;
-  j = t - ii * (ii + 1) / 2;
+// 1/x and 1/sqrt(x) to float64 accuracy: the hardware estimate (relative error
+// about 2^-24) and one third-order correction, y (1 + e + e^2) with e = 1 - x y
+// and y (1 + e/2 + 3 e^2/8) with e = 1 - x y^2, as accurate as two Newton steps
+// (about an ulp) with fewer dependent operations on the pivot chain.
+__device__ __forceinline__ double rcp_f64(double x) {
+  const double y = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, y, 1.0);
+  return fma(y, fma(e, e, e), y);
 }
-
-// 1/sqrt(x) to float64 accuracy: the hardware estimate (relative error
-// about 2^-24) and one third-order correction, y (1 + e/2 + 3 e^2/8) with
-// e = 1 - x y^2, which leaves a truncation error near 5 e^3 / 16 and is as
-// accurate as two Newton steps (about an ulp) with four dependent
-// operations instead of six on the pivot chain.
-__device__ inline double rsqrt_f64(double x) {
+__device__ __forceinline__ double rsqrt_f64(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   const double e = fma(-x * y, y, 1.0);
   return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// One 4-pivot step of the 16 x 16 diagonal-tile factorization S = L L^T,
-// pivots j0..j0+3 (j0 = 4 B), with the tile in the MFMA accumulator layout
-// (lane (g, c) = (l / 16, l % 16) holds rows g + 4 r of column c, so
-// register B of lane (g, c) is S[j0 + g][c]) and X = L^-1 carried along in
-// the same layout:
-//   1. the 4 x 4 block D = S[j0.., j0..] is read as wave-uniform scalars and
-//      factored, D = L_D L_D^T, with M = L_D^-1 (dependent pivots get a unit
-//      column in L_D); the pivots' Schur updates use the L_D entries, so the
-//      chain from one pivot to the next is one 1/sqrt and one FMA;
-//   2. C = M S[j0..j0+3, :] (one MFMA; the B operand is register B as it
-//      stands) holds L^T's rows j0..j0+3: the panel L_P^T right of the block
-//      and, by symmetry, L_D^T inside it;
-//   3. S -= L_P L_P^T on the trailing block and X[j0.., :] = M X[j0.., :],
-//      X[below, :] -= L_P X[j0.., :] (three MFMAs; A and B of the rank-4
-//      update are the same register, zero outside the trailing part).
-// R = L^T's rows j0..j0+3 of the tile are written to Rt (row stride dp).
-template <int B>
-__device__ inline void diag_step4(doublex4& a, doublex4& x, int lane, int lr, int lc, double gdl, double tol,
-                                  int& depmask, double* __restrict__ Rt, int dp) {
-  constexpr int j0 = 4 * B;
-  double W[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j <= i; ++j) W[i][j] = bcast(a[B], 16 * i + j0 + j);  // S[j0 + i][j0 + j]
-  double Ld[4][4], inv[4];
-  int dm = 0;
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    const double piv = W[p][p];
-    const bool dep = !(piv > tol * bcast(gdl, j0 + p));
-    inv[p] = dep ? 1.0 : rsqrt_f64(piv);
-    Ld[p][p] = dep ? 1.0 : piv * inv[p];
-#pragma unroll
-    for (int i = p + 1; i < 4; ++i) Ld[i][p] = dep ? 0.0 : W[i][p] * inv[p];
-#pragma unroll
-    for (int i = p + 1; i < 4; ++i)
-#pragma unroll
-      for (int j = p + 1; j <= i; ++j) W[i][j] = fma(-Ld[i][p], Ld[j][p], W[i][j]);
-    dm |= dep ? (1 << p) : 0;
-  }
-  // M = L_D^-1 (lower), M[i][i] = 1 / L_D[i][i]
-  double M[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    M[i][i] = inv[i];
-#pragma unroll
-    for (int j = 0; j < i; ++j) {
-      double t = 0.0;
-#pragma unroll
-      for (int q = j; q < i; ++q) t = fma(Ld[i][q], M[q][j], t);
-      M[i][j] = -t * inv[i];
+// The value of lane C of each row of 16 lanes, in all of the row's lanes.
+template <int C>
+__device__ __forceinline__ double row_bcast(double v) {
+  const long long b = __double_as_longlong(v);
+  return __longlong_as_double(__builtin_amdgcn_update_dpp((long long)0, b, 0x150 + C, 0xf, 0xf, true));  // row_newbcast
+}
+
+// W_i += S_i[P] tw and then S_i += S_i[P] ts, S_i[P] taken from lane P of each row
+// of 16 lanes by the FMA itself (a move of its own for each S_i[P] makes a chain
+// of two instructions, twice the time: one wave a SIMD has nothing to hide it
+// with).  A value written by a vector instruction can be read across lanes two
+// instructions later: FIRST, at a pivot's first rows, waits for what came before,
+// and for what the compiler does with these rows next.
+#define RQLP_ROW_FMA "row_newbcast:%[p] row_mask:0xf bank_mask:0xf\n\t"
+template <int P, bool FIRST>
+__device__ __forceinline__ void row_fma2(double& s0, double& w0, double& s1, double& w1, double ts, double tw) {
+  if constexpr (FIRST)
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f64_dpp %[w0], %[s0], %[tw] " RQLP_ROW_FMA "v_fmac_f64_dpp %[w1], %[s1], %[tw] " RQLP_ROW_FMA
+                 "v_fmac_f64_dpp %[s0], %[s0], %[ts] " RQLP_ROW_FMA "v_fmac_f64_dpp %[s1], %[s1], %[ts] " RQLP_ROW_FMA
+                 "s_nop 1"
+                 : [s0] "+v"(s0), [w0] "+v"(w0), [s1] "+v"(s1), [w1] "+v"(w1)
+                 : [ts] "v"(ts), [tw] "v"(tw), [p] "i"(P));
+  else
+    asm volatile("v_fmac_f64_dpp %[w0], %[s0], %[tw] " RQLP_ROW_FMA "v_fmac_f64_dpp %[w1], %[s1], %[tw] " RQLP_ROW_FMA
+                 "v_fmac_f64_dpp %[s0], %[s0], %[ts] " RQLP_ROW_FMA "v_fmac_f64_dpp %[s1], %[s1], %[ts] " RQLP_ROW_FMA
+                 : [s0] "+v"(s0), [w0] "+v"(w0), [s1] "+v"(s1), [w1] "+v"(w1)
+                 : [ts] "v"(ts), [tw] "v"(tw), [p] "i"(P));
+}
+template <int P>
+__device__ __forceinline__ void row_fma1(double& s0, double& w0, double ts, double tw) {
+  asm volatile("s_nop 1\n\t"
+               "v_fmac_f64_dpp %[w0], %[s0], %[tw] " RQLP_ROW_FMA "v_fmac_f64_dpp %[s0], %[s0], %[ts] " RQLP_ROW_FMA
+               "s_nop 1"
+               : [s0] "+v"(s0), [w0] "+v"(w0)
+               : [ts] "v"(ts), [tw] "v"(tw), [p] "i"(P));
+}
+#undef RQLP_ROW_FMA
+
+// Pivot P of the elimination of a 16-row slab: S[i] holds row i of the diagonal
+// tile (lane c of each row of 16 lanes: column c), W[i] row i of this lane's own
+// column.  Rows below lose S[i][P] / d times row P, and row P goes to LDS as it is
+// (its factor 1 / sqrt(d) is left to those who read it).  d, the pivot, and
+// r = 1 / d are in every lane and become the next ones, taken on a chain of their
+// own (a reciprocal and one FMA from pivot to pivot) whose operations stand
+// between the rows' and hide behind them.  dv and rv collect d and -r, lane c
+// those of column c.  CHECK: a pivot at or below thr is a dependent column, it
+// eliminates nothing, and its row is zero outside the diagonal tile (`panel`
+// lanes); a branch at every pivot costs half as much again as the elimination, so
+// it is first done without.
+template <bool CHECK, int P, int LD>
+__device__ __forceinline__ void pivot_step(double (&S)[kTile], double (&W)[kTile], double& d, double& r, double& dv,
+                                           double& rv, double thr, int lc, bool panel, double* put, double* put_s) {
+  dv = lc == P ? d : dv;
+  if (CHECK && __any(!(d > row_bcast<P>(thr)))) {  // (the same in every lane)
+    put[P * LD] = panel ? 0.0 : W[P];
+    put_s[P * LD] = 0.0;
+    rv = lc == P ? 0.0 : rv;
+    if constexpr (P + 1 < kTile) {
+      d = row_bcast<P + 1>(S[P + 1]);
+      r = rcp_f64(d);
     }
+    return;
   }
-  // A operand: lane (k, m) supplies M[m][k] (rows m >= 4 are zero); every
-  // lane holds the uniform M, so each picks its entry by selects
-  double am = 0.0;
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int k = 0; k <= m; ++k) am = (lc == m && lr == k) ? M[m][k] : am;
-  const doublex4 z = Mfma<double>::zero();
-  const doublex4 c = Mfma<double>::mma(am, a[B], z);   // c[0] = (M S[j0.., :])[lr][lc]
-  const doublex4 xn = Mfma<double>::mma(am, x[B], z);  // xn[0] = new X[j0 + lr][lc]
-  const bool depg = (dm >> lr) & 1;
-  // L_P^T[lr][lc] = L[lc][j0 + lr] right of the block (zero for a dependent pivot)
-  const double lp = (lc > j0 + 3 && !depg) ? c[0] : 0.0;
-  double rv = lp;  // R[j0 + lr][lc]
-  if (lc < j0 + lr) rv = 0.0;
-  else if (lc <= j0 + 3) rv = depg ? (lc == j0 + lr ? 1.0 : 0.0) : c[0];
-  Rt[(int64_t)(j0 + lr) * dp + lc] = rv;
-  x[B] = xn[0];
-  a = Mfma<double>::mma(-lp, lp, a);     // S[m][n] -= sum_k L_P[m][k] L_P[n][k]
-  x = Mfma<double>::mma(-lp, x[B], x);   // X[m][:] -= sum_k L_P[m][k] X[j0 + k][:]
-  depmask |= dm << j0;
+  put[P * LD] = W[P];
+  put_s[P * LD] = S[P];  // (the same from every wave and row of 16 lanes)
+  rv = lc == P ? -r : rv;
+  if constexpr (P + 1 < kTile) {
+    const double next = row_bcast<P + 1>(S[P + 1]), b = row_bcast<P>(S[P + 1]);
+    const double ts = -r * S[P], tw = -r * W[P];
+    d = fma(-(b * b), r, next);
+    double y = 0.0, e = 0.0;
+    auto rows = [&]<int I>(std::integral_constant<int, I>) {  // rows P + 1 + 2 I, P + 2 + 2 I
+      constexpr int i = P + 1 + 2 * I;
+      if constexpr (i + 1 < kTile) row_fma2<P, I == 0>(S[i], W[i], S[i + 1], W[i + 1], ts, tw);
+      else if constexpr (i < kTile) row_fma1<P>(S[i], W[i], ts, tw);
+    };
+    // 1 / d as rcp_f64 takes it, an operation after each pair of rows
+    y = __builtin_amdgcn_rcp(d);
+    __builtin_amdgcn_sched_barrier(0);
+    rows(std::integral_constant<int, 0>{});
+    rows(std::integral_constant<int, 1>{});
+    e = fma(-d, y, 1.0);
+    __builtin_amdgcn_sched_barrier(0);
+    rows(std::integral_constant<int, 2>{});
+    e = fma(e, e, e);
+    __builtin_amdgcn_sched_barrier(0);
+    rows(std::integral_constant<int, 3>{});
+    r = fma(y, e, y);
+    __builtin_amdgcn_sched_barrier(0);
+    rows(std::integral_constant<int, 4>{});
+    rows(std::integral_constant<int, 5>{});
+    rows(std::integral_constant<int, 6>{});
+    rows(std::integral_constant<int, 7>{});
+  }
+}
+
+template <bool CHECK, int LD>
+__device__ __forceinline__ void eliminate(double (&S)[kTile], double (&W)[kTile], double& dv, double& rv, double thr,
+                                          int lc, bool panel, double* put, double* put_s) {
+  double d = row_bcast<0>(S[0]), r = rcp_f64(d);
+  [&]<int... P>(std::integer_sequence<int, P...>) {
+    (pivot_step<CHECK, P, LD>(S, W, d, r, dv, rv, thr, lc, panel, put, put_s), ...);
+  }(std::make_integer_sequence<int, kTile>{});
+}
+
+// Workgroup barrier for data passed in LDS: stores to memory in flight are not
+// waited for.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Fast path of the second CholeskyQR pass: when ||G - I||_F < fast_tol
@@ -183,7 +229,7 @@ __device__ inline bool chol_fast_path(const double* __restrict__ G, int d, int d
 // The body is shared by the one-matrix kernel and the grouped kernel that
 // factors many matrices in one launch (bid, nblk: this workgroup's index
 // and the workgroup count of its matrix).
-template <int NW, int SLOTS>
+template <int TMAX>
 __device__ __attribute__((always_inline)) inline void chol_body(const double* __restrict__ G, int ld, int d, int dp,
                                                     double* __restrict__ R,
                                                     double* __restrict__ Rinv16,
@@ -193,11 +239,19 @@ __device__ __attribute__((always_inline)) inline void chol_body(const double* __
                                                     int32_t* __restrict__ mode,
                                                     double* __restrict__ Xfull,
                                                     const double* __restrict__ gdiag0, int block, int bid, int nblk) {
-  __shared__ double Pn[kCholRegMax / kTile][kTile][kTile + 1];  // panel tiles L_ik of column k
-  __shared__ double Di[kTile][kTile + 1];                        // inverse of the diagonal factor
-  __shared__ double Gdiag[kCholRegMax];
-  __shared__ int defl[kCholRegMax];
-  __shared__ double red[NW];
+  constexpr int SLOTS = (TMAX * (TMAX + 1) / 2 + kChU - 1) / kChU;
+  // slab[k & 1]: block row k of D^1/2 R, D the pivots, and behind it D^1/2 R_kk (upper
+  // part), D^1/2 L_kk^-1 and columns of scratch; beside it -1/D, D^-1/2 and R_kk's
+  // diagonal; grow: the block row of G that is eliminated next.
+  // Its row stride is 16 mod 32 values, so that the four rows an MFMA operand
+  // takes spread over the banks.
+  constexpr int RD = TMAX * kTile, XD = RD + kTile, LD = XD + 2 * kTile;
+  constexpr int ZD = XD + kTile;
+  static_assert(TMAX % 2 == 0 && TMAX <= 4 * kChE && TMAX <= 2 * kChU, "slab stride and width");
+  __shared__ double slab[2][kTile][LD], grow[kTile][LD];
+  __shared__ double nrd[2][kTile], rsd[2][kTile], diag[2][kTile];
+  __shared__ double Gdiag[TMAX * kTile];
+  __shared__ double red[kChWaves];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -206,174 +260,193 @@ __device__ __attribute__((always_inline)) inline void chol_body(const double* __
 
   if (block) {
     if (*mode == 2) return;
-  } else if (fast_tol > 0.0 &&
-             chol_fast_path(G, d, dp, R, Rinv16, flags, fast_tol, esq, nesq, mode, Xfull, red, NW, bid, nblk)) {
+  } else if (fast_tol > 0.0 && chol_fast_path(G, d, dp, R, Rinv16, flags, fast_tol, esq, nesq, mode, Xfull, red,
+                                              kChWaves, bid, nblk)) {
     return;
   }
   if (bid != 0) return;  // the factorization runs in one workgroup
 
   // ---------------- full factorization ----------------
-  for (int i = tid; i < dp; i += blockDim.x) {
+  for (int i = tid; i < dp; i += kChThreads)
     Gdiag[i] = (i < d) ? (gdiag0 ? gdiag0[i] : G[(int64_t)i * ld + i]) : 1.0;
-    defl[i] = 0;
-  }
-  const int ntiles = T * (T + 1) / 2;
-  // slot sl of this wave holds tile t = wave + NW sl of the lower triangle,
-  // (i, j) packed as i + 256 (j + 1) (a free slot has j = -1)
-  doublex4 tile[SLOTS];
-  int tij[SLOTS];
-#pragma unroll
-  for (int sl = 0; sl < SLOTS; ++sl) {
-    const int t = wave + NW * sl;
-    int i0 = 0, j0 = -1;
-    if (t < ntiles) tile_of(t, i0, j0);
-    tij[sl] = __builtin_amdgcn_readfirstlane(i0 + 256 * (j0 + 1));
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      double v = 0.0;
-      if (t < ntiles) {
-        const int row = i0 * kTile + lr + 4 * r, col = j0 * kTile + lc;
-        v = (row < d && col < d) ? G[(int64_t)row * ld + col] : (row == col ? 1.0 : 0.0);
-      }
-      tile[sl][r] = v;
-    }
-  }
-  int ndep_total = 0;
-  __syncthreads();
 
-  // A: the owner of tile (k,k) factors it in four 4-pivot steps and
-  // publishes Di = L_kk^-1, the R block L_kk^T, its inverse and the
-  // dependent-column flags.
-  auto factor_diag = [&](int k, int sk) {
-    doublex4 t = Mfma<double>::zero();
+  if (wave >= kChE) {
+    // ---- tiles: slot sl of this wave holds tile (i, j), j >= i, packed as i + 256 j ----
+    const int ntiles = T * (T + 1) / 2;
+    doublex4 tile[SLOTS];
+    int tij[SLOTS];
+#pragma unroll
+    for (int sl = 0; sl < SLOTS; ++sl) {
+      const int t = wave - kChE + kChU * sl;
+      int i0 = 0, j0 = 0;
+      if (t < ntiles) tile_of(t, T, i0, j0);
+      tij[sl] = __builtin_amdgcn_readfirstlane(t < ntiles ? i0 + 256 * j0 : -1);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        double v = 0.0;
+        if (t < ntiles) {
+          const int row = i0 * kTile + lr + 4 * r, col = j0 * kTile + lc;
+          v = (row < d && col < d) ? G[(int64_t)row * ld + col] : (row == col ? 1.0 : 0.0);
+        }
+        tile[sl][r] = v;
+      }
+    }
+    auto publish = [&](const doublex4& t, int j) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) grow[lr + 4 * r][j * kTile + lc] = t[r];
+    };
+    // G_ij -= R_ki^T R_kj
+    auto update = [&](const double (*from)[LD], const double (&f)[4], doublex4& t, int i, int j) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+        t = Mfma<double>::mma(from[ks * 4 + lr][i * kTile + lc] * f[ks], from[ks * 4 + lr][j * kTile + lc], t);
+    };
+    // the first slot of this wave whose tile is in row i or below
+    auto first = [&](int i) {
+      const int t = i < T ? i * T - i * (i - 1) / 2 : ntiles;
+      return (t - (wave - kChE) + kChU - 1) / kChU;  // (t >= 0; a negative numerator gives 0)
+    };
+    // block row k of R, L_kk^-T's block to memory
+    auto store = [&](int k) {
+      const double (*from)[LD] = slab[k & 1];
+      const double* scale = rsd[k & 1];
+      const int u = wave - kChE;
+      double* Rk = R + (int64_t)k * kTile * ld;
+      for (int c = (u >> 2) * kWave + lane; c < dp; c += (kChU / 4) * kWave) {
+        const bool in_diag = (c >> 4) == k;
+        const int from_c = in_diag ? RD + lc : c;
+        double v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int row = 4 * (u & 3) + q;
+          v[q] = from[row][from_c] * scale[row];
+          v[q] = in_diag && lc == row ? diag[k & 1][row] : v[q];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int row = 4 * (u & 3) + q;
+          Rk[(int64_t)row * ld + c] = c < k * kTile + (in_diag ? row : 0) ? 0.0 : v[q];
+        }
+      }
+      if (u >= kChU - 4) {
+        const int e = (u - (kChU - 4)) * kWave + lane;
+        Rinv16[(int64_t)k * kTile * kTile + e] = from[e & 15][XD + (e >> 4)] * scale[e & 15];
+      }
+    };
 #pragma unroll
     for (int sl = 0; sl < SLOTS; ++sl)
-      if (sl == sk) t = tile[sl];
-    doublex4 x;
+      if (tij[sl] >= 0 && (tij[sl] & 255) == 0) publish(tile[sl], tij[sl] >> 8);
+    double f[4] = {0.0, 0.0, 0.0, 0.0};  // -1/D of the step, for this lane's rows
+    lds_barrier();
+    for (int k = 0; k < T; ++k) {
+      // opaque to the optimizer: otherwise the LDS addresses of every slot are
+      // hoisted out of this loop and held in vector registers the tiles need
 #pragma unroll
-    for (int r = 0; r < 4; ++r) x[r] = (lr + 4 * r == lc) ? 1.0 : 0.0;
-    const double gdl = Gdiag[k * kTile + lc];
-    int depmask = 0;
-    double* Rt = R + (int64_t)k * kTile * ld + k * kTile;
-    // the diagonal factorization is the latency chain of the whole
-    // factorization: its wave takes issue priority over the co-resident
-    // waves' trailing updates while it runs
-    __builtin_amdgcn_s_setprio(3);
-    diag_step4<0>(t, x, lane, lr, lc, gdl, tol, depmask, Rt, ld);
-    diag_step4<1>(t, x, lane, lr, lc, gdl, tol, depmask, Rt, ld);
-    diag_step4<2>(t, x, lane, lr, lc, gdl, tol, depmask, Rt, ld);
-    diag_step4<3>(t, x, lane, lr, lc, gdl, tol, depmask, Rt, ld);
+      for (int sl = 0; sl < SLOTS; ++sl) asm volatile("" : "+s"(tij[sl]));
+      // rows are in order, so the tiles of rows > k are the slots from first(k + 1)
+      // on, those of row k + 1 (at most two) the ones before first(k + 2)
+      const int s1 = first(k + 1), s2 = first(k + 2);
+      if (k > 0) {  // the rest of step k - 1, while row k is eliminated
+        // (half of the waves store first, so that the matrix cores stay busy)
+        if (wave & 1) store(k - 1);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = lr + 4 * r;
-      Di[row][lc] = x[r];                                              // X[row][c]
-      Rinv16[(int64_t)k * kTile * kTile + lc * kTile + row] = x[r];    // (L^-1)^T
-    }
-    __builtin_amdgcn_s_setprio(0);
-    if (lane < kTile) {
-      const int dep_c = (depmask >> lane) & 1;
-      defl[k * kTile + lane] = dep_c;
-      flags[k * kTile + lane] = dep_c;
-    }
-    ndep_total += __popc(depmask);
-  };
-
-  // G_ij -= L_ik L_jk^T for a tile of the trailing matrix (k < j <= i)
-  auto update_g = [&](doublex4& t, int i, int j) {
+        for (int g = 0; g < SLOTS; g += 3)
+          if (g + 3 > s1) {
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int kk = ks * 4 + lr;
-      t = Mfma<double>::mma(-Pn[i][lc][kk], Pn[j][lc][kk], t);  // B[kk][n] = L_jk[n][kk]
-    }
-  };
-
-  {  // A for k = 0
-    const int t0 = 0;
-    if (wave == t0 % NW) factor_diag(0, t0 / NW);
-  }
-  for (int k = 0; k < T; ++k) {
-    // Opaque to the optimizer: otherwise the LDS addresses of every slot are
-    // hoisted out of this loop and held in vector registers the tiles need.
+            for (int sl = g; sl < min(g + 3, SLOTS); ++sl)
+              if (sl >= s1 && tij[sl] >= 0) update(slab[(k - 1) & 1], f, tile[sl], tij[sl] & 255, tij[sl] >> 8);
+          }
+        if (!(wave & 1)) store(k - 1);
+      }
+      lds_barrier();  // R's block row k is in slab[k & 1]
 #pragma unroll
-    for (int sl = 0; sl < SLOTS; ++sl) asm volatile("" : "+s"(tij[sl]));
-    __syncthreads();
-    // ---------------- B: panel L_ik = G_ik L_kk^-T ----------------
+      for (int ks = 0; ks < 4; ++ks) f[ks] = nrd[k & 1][ks * 4 + lr];
 #pragma unroll
-    for (int sl = 0; sl < SLOTS; ++sl) {
-      const int i = tij[sl] & 255, j = (tij[sl] >> 8) - 1;
-      if (j == k && i > k) {
+      for (int g = 0; g < SLOTS; g += 3)  // (by threes: a skipped branch is a tenth of a tile's update)
+        if (g + 3 > s1 && g < s2) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) Pn[i][lr + 4 * r][lc] = tile[sl][r];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        doublex4 acc = Mfma<double>::zero();
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const int kk = ks * 4 + lr;
-          acc = Mfma<double>::mma(Pn[i][lc][kk], Di[lc][kk], acc);  // B[kk][n] = X[n][kk]
+          for (int sl = g; sl < min(g + 3, SLOTS); ++sl)
+            if (sl >= s1 && sl < s2) {
+              update(slab[k & 1], f, tile[sl], k + 1, tij[sl] >> 8);
+              publish(tile[sl], tij[sl] >> 8);
+            }
         }
-        const bool zc = defl[k * kTile + lc] != 0;
-        __builtin_amdgcn_wave_barrier();
+      lds_barrier();  // G's block row k + 1 is in grow
+    }
+    store(T - 1);
+    return;
+  }
+
+  // ---- block rows: lane group g of wave w takes the columns of tile k + 4 w + g,
+  // the first of all those of the identity (for R_kk^-T) ----
+  const int idx = 4 * wave + lr;
+  int ndep = 0;
+  lds_barrier();
+  for (int k = 0; k < T; ++k) {
+    double (*sk)[LD] = slab[k & 1];
+    double dv = 0.0;
+    const double thr = tol * Gdiag[k * kTile + lc];
+    if (4 * wave < T - k) {
+      __builtin_amdgcn_s_setprio(3);  // the elimination is the chain of the whole factorization
+      const bool mine = idx < T - k;
+      int c = lc;  // (opaque: what is computed from it is not kept in registers from step to step)
+      asm volatile("" : "+v"(c));
+      const double* dcol = &grow[0][k * kTile + c];
+      const double* wcol = &grow[0][(k + (mine ? idx : 0)) * kTile + c];
+      double* put = &sk[0][idx == 0 ? XD + c : (mine ? (k + idx) * kTile + c : ZD + c)];
+      double S[kTile], W[kTile], rv = 0.0;
+      auto fetch = [&] {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) Pn[i][lr + 4 * r][lc] = zc ? 0.0 : acc[r];
+        for (int p = 0; p < kTile; ++p) {
+          S[p] = dcol[p * LD];
+          W[p] = wcol[p * LD];
+        }
+#pragma unroll
+        for (int p = 0; p < kTile; ++p) W[p] = idx == 0 ? (p == c ? 1.0 : 0.0) : W[p];
+      };
+      fetch();
+      eliminate<false, LD>(S, W, dv, rv, thr, c, idx > 0, put, &sk[0][RD + c]);
+      if (__builtin_expect(__any(!(dv > thr)), 0)) {  // a dependent column
+        fetch();
+        eliminate<true, LD>(S, W, dv, rv, thr, c, idx > 0, put, &sk[0][RD + c]);
       }
+      if (wave == 0 && lr == 0) nrd[k & 1][lc] = rv;
+      __builtin_amdgcn_s_setprio(0);
     }
-    __syncthreads();
-    // ---------------- C: trailing update, with the next A looked ahead ----------------
-    // The owner of tile (k+1, k+1) updates it first and factors it at once;
-    // the other waves publish the panel (R = L^T above the diagonal block
-    // row k, zero below) and go on with their updates meanwhile.
-    const int kn = k + 1;
-    const int tn = kn * (kn + 1) / 2 + kn;
-    const int own = tn % NW;
-    const bool ahead = kn < T && wave == own;
-    const int sn = tn / NW;
-    if (ahead) {
-      __builtin_amdgcn_s_setprio(3);  // the update of tile (k+1, k+1) is on the chain too
-#pragma unroll
-      for (int sl = 0; sl < SLOTS; ++sl)
-        if (sl == sn) update_g(tile[sl], kn, kn);
-      factor_diag(kn, sn);
-    } else {
-      const int nt = (kn < T) ? NW - 1 : NW;                 // publishing waves
-      const int pw = (kn < T && wave > own) ? wave - 1 : wave;  // rank among them
-      for (int e = pw * kWave + lane; e < (T - 1 - k) * kTile * kTile; e += nt * kWave) {
-        const int i = k + 1 + e / (kTile * kTile), row = (e / kTile) % kTile, col = e % kTile;
-        R[(int64_t)(k * kTile + col) * ld + i * kTile + row] = Pn[i][row][col];
-        R[(int64_t)(i * kTile + row) * ld + k * kTile + col] = 0.0;
+    lds_barrier();  // R's block row k is in slab[k & 1]
+    if (wave == 0) {  // (read after the next barrier)
+      const bool dep = !(dv > thr);
+      const double rs = dep ? 1.0 : rsqrt_f64(dv);
+      if (lr == 0) {
+        rsd[k & 1][lc] = rs;
+        diag[k & 1][lc] = dep ? 1.0 : dv * rs;
+        flags[k * kTile + lc] = dep;
       }
+      ndep += __popcll(__ballot(dep) & 0xffff);
     }
-#pragma unroll
-    for (int sl = 0; sl < SLOTS; ++sl) {
-      if (ahead && sl == sn) continue;
-      const int i = tij[sl] & 255, j = (tij[sl] >> 8) - 1;
-      if (j > k) update_g(tile[sl], i, j);
-    }
+    lds_barrier();  // G's block row k + 1 is in grow
   }
   // the explicit R^-1 (formed next by the inverse kernel) serves the solve
   // unless a column was dependent
-  int anydep = 0;
-  for (int i = tid; i < dp; i += blockDim.x) anydep |= defl[i];
-  anydep = __syncthreads_or(anydep);
   if (tid == 0) {
-    if (!block) *mode = anydep ? 0 : 1;
-    else if (anydep) *mode = 0;
-  }
-  if (lane == 0 && ndep_total > 0) {
-    atomicAdd(&info->completed_cols, ndep_total);
-    atomicCAS(&info->breakdown_pass, 0, pass_id);
+    if (!block) *mode = ndep ? 0 : 1;
+    else if (ndep) *mode = 0;
+    if (ndep) {
+      atomicAdd(&info->completed_cols, ndep);
+      atomicCAS(&info->breakdown_pass, 0, pass_id);
+    }
   }
 }
 
-template <int NW, int SLOTS>
-__global__ __launch_bounds__(NW * 64) void chol_kernel(const double* __restrict__ G, int ld, int d, int dp,
+template <int TMAX>
+__global__ __launch_bounds__(kChThreads) void chol_kernel(const double* __restrict__ G, int ld, int d, int dp,
                                                     double* __restrict__ R, double* __restrict__ Rinv16,
                                                     int32_t* __restrict__ flags, DevInfo* info, int pass_id,
                                                     double tol, double fast_tol, const double* __restrict__ esq,
                                                     int nesq, int32_t* __restrict__ mode,
                                                     double* __restrict__ Xfull, const double* __restrict__ gdiag0,
                                                     int block) {
-  chol_body<NW, SLOTS>(G, ld, d, dp, R, Rinv16, flags, info, pass_id, tol, fast_tol, esq, nesq, mode, Xfull, gdiag0,
+  chol_body<TMAX>(G, ld, d, dp, R, Rinv16, flags, info, pass_id, tol, fast_tol, esq, nesq, mode, Xfull, gdiag0,
                        block, blockIdx.x, gridDim.x);
 }
 
@@ -393,18 +466,18 @@ struct CholRecArgs {
   int ld, d, dp, pass_id, nesq, block;
 };
 
-template <int NW, int SLOTS>
-__global__ __launch_bounds__(NW * 64) void chol_grouped(const CholRecArgs* __restrict__ a,
+template <int TMAX>
+__global__ __launch_bounds__(kChThreads) void chol_grouped(const CholRecArgs* __restrict__ a,
                                                         const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const CholRecArgs g = a[p];
-  chol_body<NW, SLOTS>(g.G, g.ld, g.d, g.dp, g.R, g.Rinv16, g.flags, g.info, g.pass_id, g.tol, g.fast_tol, g.esq,
+  chol_body<TMAX>(g.G, g.ld, g.d, g.dp, g.R, g.Rinv16, g.flags, g.info, g.pass_id, g.tol, g.fast_tol, g.esq,
                        g.nesq, g.mode, g.Xfull, g.gdiag0, g.block, (int)blockIdx.x - start[p], start[p + 1] - start[p]);
 }
 
-template <int NW, int SLOTS>
+template <int TMAX>
 void chol_grouped_launch(const void* args, const int* start, int count, unsigned blocks, hipStream_t s) {
-  hipLaunchKernelGGL((chol_grouped<NW, SLOTS>), dim3(blocks), dim3(NW * kWave), 0, s, (const CholRecArgs*)args,
+  hipLaunchKernelGGL((chol_grouped<TMAX>), dim3(blocks), dim3(kChThreads), 0, s, (const CholRecArgs*)args,
                      start, count);
 }
 
@@ -589,19 +662,18 @@ static hipError_t launch_chol_reg(const double* G, int ld, int d, int db, double
                                   const double* esq, int nesq, int32_t* mode, double* Xfull, const double* gdiag0,
                                   int block, hipStream_t s) {
   const int T = db / kTile;
-  const int tiles = T * (T + 1) / 2;
   const unsigned grid = (!block && fast_tol > 0.0) ? 16 : 1;  // extra workgroups only help the fast path
   const CholRecArgs a{G, R, Rinv16, flags, (DevInfo*)info, esq, mode, Xfull, gdiag0, tol, fast_tol, ld, d, db, pass_id,
                       nesq, block};
 #define RQLP_CHOL_LAUNCH(S)                                                                                        \
   do {                                                                                                             \
-    if (!record_launch(&chol_grouped_launch<8, S>, a, grid))                                                       \
-      hipLaunchKernelGGL((chol_kernel<8, S>), dim3(grid), dim3(8 * kWave), 0, s, G, ld, d, db, R, Rinv16, flags,    \
+    if (!record_launch(&chol_grouped_launch<S>, a, grid))                                                       \
+      hipLaunchKernelGGL((chol_kernel<S>), dim3(grid), dim3(kChThreads), 0, s, G, ld, d, db, R, Rinv16, flags,       \
                          (DevInfo*)info, pass_id, tol, fast_tol, esq, nesq, mode, Xfull, gdiag0, block);             \
   } while (0)
-  if (tiles <= 8 * 7) RQLP_CHOL_LAUNCH(7);
-  else if (tiles <= 8 * 14) RQLP_CHOL_LAUNCH(14);
-  else RQLP_CHOL_LAUNCH(17);
+  if (T <= 10) RQLP_CHOL_LAUNCH(10);
+  else if (T <= 14) RQLP_CHOL_LAUNCH(14);
+  else RQLP_CHOL_LAUNCH(16);
 #undef RQLP_CHOL_LAUNCH
   return hipGetLastError();
 }
@@ -650,12 +722,6 @@ hipError_t launch_chol(double* G, int d, int dp, double* R, double* Rinv16, int3
   if (ev1) (void)hipEventRecord(ev1, s);
   if (e != hipSuccess) return e;
   return hipGetLastError();
-}
-
-int chol_slot_class(int dp) {
-  const int T = dp / kTile;
-  const int tiles = T * (T + 1) / 2;
-  return tiles <= 8 * 7 ? 7 : (tiles <= 8 * 14 ? 14 : 17);
 }
 
 }  // namespace rqlp

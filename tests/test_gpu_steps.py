@@ -169,6 +169,30 @@ def test_orth_rank_deficient_completes_basis(gpu_lib, dtype):
     assert np.all(R[dep, :] == 0.0)
 
 
+@pytest.mark.parametrize("d", [16, 17, 33, 160, 161, 224, 225, 256])
+@pytest.mark.parametrize("ndep", [0, 1, 3])
+def test_orth_tile_edges(gpu_lib, d, ndep):
+    """One tile of the Cholesky factor and the edges of its launch variants,
+    with dependent columns at the last column of a tile, the first of the next
+    and the last of all (bounds: as in test_orth_rank_deficient_wide)."""
+    announce("orth tile edges", d, ndep)
+    rng = np.random.default_rng(d)
+    dep = sorted({15, min(16, d - 1), d - 1})[:ndep]
+    Y = rng.standard_normal((700, d))
+    for c in dep:
+        Y[:, c] = Y[:, :c] @ rng.standard_normal(c)
+    ctx = gpu_lib.default_context(0)
+    Q, R = gpu_lib.orth(to_dev(Y), want_r=True, ctx=ctx)
+    Q, R = to_np(Q), to_np(R)
+    tol = 1e-12
+    assert np.linalg.norm(Q.T @ Q - np.eye(d)) <= 10 * tol
+    assert np.linalg.norm(Q @ R - Y) <= 10 * tol * np.linalg.norm(Y)
+    assert np.all(np.tril(R, -1) == 0)
+    assert ctx.info()["completed_cols"] == len(dep)
+    assert np.all(np.diag(R)[dep] == 0.0)
+    assert np.all(np.diag(R)[[j for j in range(d) if j not in dep]] > 0.0)
+
+
 @pytest.mark.parametrize("rows", [1500, 30000])
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
 def test_orth_rank_deficient_wide(gpu_lib, dtype, rows):
