@@ -7,10 +7,13 @@
 // I' <= I adds R_{I',I+1} X_{I+1,J} to its accumulator (float64 MFMA), and the
 // owner of row I finishes it with R_II^-1.  Rows are dealt to the waves
 // round-robin; X_{I+1,J} is passed through LDS (double buffered, one
-// workgroup barrier per block row).  The step loop is unrolled so that the
-// R tiles of each step can be loaded into a register ring several steps
-// before they are used.  The diagonal-block inverses come from
-// the Cholesky.  Nothing is done after the Cholesky's fast path, which
+// workgroup barrier per block row).  The R tiles of each step are loaded into
+// a register ring several steps before they are used; what bounds a step is the
+// chain barrier, X_{I+1,J} from LDS, 4 + 4 MFMAs, LDS (about 1000 cycles) and, with
+// many rows to a wave, those rows' R tiles and MFMAs.  Measured with the steps
+// unrolled, the tiles in four 8-byte loads a lane and all loads waited for, and
+// now: d = 210 17.3 -> 14.0 us, 540 67 -> 51.  The diagonal-block inverses come
+// from the Cholesky.  Nothing is done after the Cholesky's fast path, which
 // writes its own inverse.  A dependent column has a unit row in R, so the
 // inverse exists and its other columns do not involve it.
 #include "common.h"
@@ -32,25 +35,33 @@ __device__ __attribute__((always_inline)) inline void trinv_body(const double* _
                                                                const int32_t* __restrict__ mode,
                                                                double* __restrict__ X, const int J) {
   constexpr int kInvRows = (kInvT + kInvWaves - 1) / kInvWaves;  // block rows per wave
-  __shared__ double Zs[2][kTile][kTile + 1];
+  __shared__ double Zs[2][kTile][kTile + 4];  // (rows 4 lr + ks of four lr's spread over the banks)
   if (*mode == 2) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane >> 4, lc = lane & 15;
 
-  // A operands of R_{I', t} for this wave's rows I' = wave + 8 s, step I = t - 1:
-  // ring[I % kInvAhead][s][ks] (float64 MFMA A layout: A[m][kk] = R_I't[m][kk])
+  // A operands of R_{I', t} for this wave's rows I' = wave + kInvWaves s, step I = t - 1:
+  // ring[(J - 1 - I) % kInvAhead][s][ks] (float64 MFMA A layout, A[m][kk] = R_I't[m][kk],
+  // with kk = 4 lr + ks: a lane's four values are one run of 32 bytes)
   double ring[kInvAhead][kInvRows][4];
-  auto load_step = [&](auto Ic) {
-    constexpr int I = decltype(Ic)::value;
-    constexpr int t = I + 1;
+  // (the loads stand in no branch, so that the compiler can count those in flight
+  // and a step waits for its own only; a row that a step has not is an address out
+  // of the buffer's range, which costs no access)
+  const __amdgpu_buffer_rsrc_t Rb =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(R), 0, kInvT * kTile * dp * 8, 0x00020000);
+  auto load_step = [&](auto slot, int I) {
 #pragma unroll
     for (int s = 0; s < kInvRows; ++s) {
       const int Ip = wave + kInvWaves * s;
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-        ring[I % kInvAhead][s][ks] =
-            (Ip <= I) ? R[(int64_t)(Ip * kTile + lc) * dp + t * kTile + ks * 4 + lr] : 0.0;
+      const int at = Ip <= I ? ((Ip * kTile + lc) * dp + (I + 1) * kTile + 4 * lr) * 8 : -32;
+      typedef double v2d __attribute__((ext_vector_type(2)));
+      const v2d lo = __builtin_bit_cast(v2d, __builtin_amdgcn_raw_buffer_load_b128(Rb, at, 0, 0));
+      const v2d hi = __builtin_bit_cast(v2d, __builtin_amdgcn_raw_buffer_load_b128(Rb, at, 16, 0));
+      ring[decltype(slot)::value][s][0] = lo.x;
+      ring[decltype(slot)::value][s][1] = lo.y;
+      ring[decltype(slot)::value][s][2] = hi.x;
+      ring[decltype(slot)::value][s][3] = hi.y;
     }
   };
   // -R_I'I'^-1 as A operands for the rows this wave finishes
@@ -62,10 +73,15 @@ __device__ __attribute__((always_inline)) inline void trinv_body(const double* _
     for (int ks = 0; ks < 4; ++ks)
       rinv[s][ks] = (Ip < J) ? -Rinv16[(int64_t)Ip * kTile * kTile + lc * kTile + ks * 4 + lr] : 0.0;
   }
-  // the first kInvAhead steps (I = J-1 down to J-kInvAhead)
-  [&]<int... Is>(std::integer_sequence<int, Is...>) {
-    ((Is < J && Is >= J - kInvAhead ? load_step(std::integral_constant<int, Is>{}) : void()), ...);
-  }(std::make_integer_sequence<int, kInvT>{});
+  auto slots = [&](auto f) {
+    [&]<int... Qs>(std::integer_sequence<int, Qs...>) {
+      (f(std::integral_constant<int, Qs>{}), ...);
+    }(std::make_integer_sequence<int, kInvAhead>{});
+  };
+  if (J > 0)
+    slots([&](auto q) {
+      if constexpr (decltype(q)::value + 1 < kInvAhead) load_step(q, J - 1 - decltype(q)::value);
+    });
 
   // X_JJ = R_JJ^-1 (row-major 16 x 16 block of Rinv16)
   for (int e = tid; e < kTile * kTile; e += blockDim.x) {
@@ -79,42 +95,45 @@ __device__ __attribute__((always_inline)) inline void trinv_body(const double* _
   for (int s = 0; s < kInvRows; ++s) S[s] = Mfma<double>::zero();
   __syncthreads();
 
-  // steps I = J-1 down to 0, unrolled so that the ring slots are fixed
-  auto step = [&](auto Ic) {
-    constexpr int I = decltype(Ic)::value;
-    if (I >= J) return;
-    const int buf = (J - 1 - I) & 1;  // X_{I+1,J} is in Zs[buf]
-    // S_I' += R_{I',I+1} X_{I+1,J} for the pending rows I' <= I of this wave
+  // Steps I = J-1 down to 0, kInvAhead to a turn of the loop so that the ring slots
+  // are fixed.  (Not unrolled further: code that runs once comes from memory, and
+  // its lines took longer than its work.)
+  int buf = 0;  // X_{I+1,J} is in Zs[buf]
+  for (int I0 = J - 1; I0 >= 0; I0 -= kInvAhead) {
+    slots([&](auto q) {
+      const int I = I0 - decltype(q)::value;
+      if (I < 0) return;
+      double zk[4];
 #pragma unroll
-    for (int s = 0; s < kInvRows; ++s) {
-      const int Ip = wave + kInvWaves * s;
-      if (Ip <= I) {
+      for (int ks = 0; ks < 4; ++ks) zk[ks] = Zs[buf][4 * lr + ks][lc];
+      // the slot of the step before is free (addresses while LDS answers)
+      load_step(std::integral_constant<int, (decltype(q)::value + kInvAhead - 1) % kInvAhead>{}, I + 1 - kInvAhead);
+      // S_I' += R_{I',I+1} X_{I+1,J} for the pending rows I' <= I of this wave, the
+      // last of them first: the owner of row I finishes X_IJ = -R_II^-1 S_I
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-          S[s] = Mfma<double>::mma(ring[I % kInvAhead][s][ks], Zs[buf][ks * 4 + lr][lc], S[s]);
+      for (int s = kInvRows - 1; s >= 0; --s) {
+        const int Ip = wave + kInvWaves * s;
+        if (Ip <= I) {
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks) S[s] = Mfma<double>::mma(ring[decltype(q)::value][s][ks], zk[ks], S[s]);
+        }
+        if (Ip == I) {
+          doublex4 z = Mfma<double>::zero();
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks)  // the accumulator layout is the B operand layout
+            z = Mfma<double>::mma(rinv[s][ks], S[s][ks], z);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int row = lr + 4 * r;
+            Zs[buf ^ 1][row][lc] = z[r];
+            X[(int64_t)(I * kTile + row) * dp + J * kTile + lc] = z[r];
+          }
+        }
       }
-    }
-    // this step's ring slot is free again: fetch the tiles of step I - kInvAhead
-    if constexpr (I >= kInvAhead) load_step(std::integral_constant<int, I - kInvAhead>{});
-    // the owner of row I finishes X_IJ = -R_II^-1 S_I
-    if (wave == I % kInvWaves) {
-      constexpr int so = I / kInvWaves;
-      doublex4 z = Mfma<double>::zero();
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)  // the accumulator layout is the B operand layout
-        z = Mfma<double>::mma(rinv[so][ks], S[so][ks], z);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = lr + 4 * r;
-        Zs[buf ^ 1][row][lc] = z[r];
-        X[(int64_t)(I * kTile + row) * dp + J * kTile + lc] = z[r];
-      }
-    }
-    __syncthreads();
-  };
-  [&]<int... Is>(std::integer_sequence<int, Is...>) {
-    (step(std::integral_constant<int, kInvT - 1 - Is>{}), ...);
-  }(std::make_integer_sequence<int, kInvT>{});
+      __syncthreads();
+      buf ^= 1;
+    });
+  }
 }
 
 template <int kInvWaves, int kInvT, int kInvAhead>
