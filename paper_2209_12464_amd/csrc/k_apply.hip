@@ -220,8 +220,9 @@ __global__ __launch_bounds__(256) void apply_grouped(const ApplyArgs* __restrict
   const int p = group_find(start, count, blockIdx.x);
   const ApplyArgs g = a[p];
   const int b = (int)blockIdx.x - start[p];
-  apply_body<Tin, Tout, RF>((const Tin*)g.Y, g.ldy, g.rows, g.d, g.dp, g.flags, g.mode, g.X, (Tout*)g.out1, g.ld1,
-                            g.ncols1, (Tout*)g.out2, g.ld2, g.ncols2, g.seed, g.key1, g.isr, b % g.gx, b / g.gx);
+  apply_body<Tin, Tout, RF>(device_ptr((const Tin*)g.Y), g.ldy, g.rows, g.d, g.dp, device_ptr(g.flags),
+                            device_ptr(g.mode), device_ptr(g.X), device_ptr((Tout*)g.out1), g.ld1, g.ncols1,
+                            device_ptr((Tout*)g.out2), g.ld2, g.ncols2, g.seed, g.key1, g.isr, b % g.gx, b / g.gx);
 }
 
 template <typename Tin, typename Tout, int RF>
@@ -294,8 +295,9 @@ __global__ __launch_bounds__(256) void apply_f32fast_grouped(const ApplyArgs* __
   const int p = group_find(start, count, blockIdx.x);
   const ApplyArgs g = a[p];
   const int b = (int)blockIdx.x - start[p];
-  apply_f32fast_body<RF>((const double*)g.Y, g.ldy, g.rows, g.d, g.dp, g.flags, g.mode, g.X, (float*)g.out1, g.ld1,
-                         g.ncols1, (float*)g.out2, g.ld2, g.ncols2, g.seed, g.key1, g.isr, b % g.gx, b / g.gx);
+  apply_f32fast_body<RF>(device_ptr((const double*)g.Y), g.ldy, g.rows, g.d, g.dp, device_ptr(g.flags),
+                         device_ptr(g.mode), device_ptr(g.X), device_ptr((float*)g.out1), g.ld1, g.ncols1,
+                         device_ptr((float*)g.out2), g.ld2, g.ncols2, g.seed, g.key1, g.isr, b % g.gx, b / g.gx);
 }
 
 template <int RF>

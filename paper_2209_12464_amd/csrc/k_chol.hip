@@ -471,8 +471,10 @@ __global__ __launch_bounds__(kChThreads) void chol_grouped(const CholRecArgs* __
                                                         const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const CholRecArgs g = a[p];
-  chol_body<TMAX>(g.G, g.ld, g.d, g.dp, g.R, g.Rinv16, g.flags, g.info, g.pass_id, g.tol, g.fast_tol, g.esq,
-                       g.nesq, g.mode, g.Xfull, g.gdiag0, g.block, (int)blockIdx.x - start[p], start[p + 1] - start[p]);
+  chol_body<TMAX>(device_ptr(g.G), g.ld, g.d, g.dp, device_ptr(g.R), device_ptr(g.Rinv16), device_ptr(g.flags),
+                  device_ptr(g.info), g.pass_id, g.tol, g.fast_tol, device_ptr(g.esq), g.nesq, device_ptr(g.mode),
+                  device_ptr(g.Xfull), device_ptr(g.gdiag0), g.block, (int)blockIdx.x - start[p],
+                  start[p + 1] - start[p]);
 }
 
 template <int TMAX>
@@ -534,7 +536,8 @@ __global__ __launch_bounds__(1024) void chol_prep_grouped(const CholPrepArgs* __
                                                        const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const CholPrepArgs g = a[p];
-  chol_prep_body(g.G, g.d, g.dp, g.R, g.Rinv16, g.flags, g.fast_tol, g.esq, g.nesq, g.mode, g.Xfull, g.gd0,
+  chol_prep_body(device_ptr(g.G), g.d, g.dp, device_ptr(g.R), device_ptr(g.Rinv16), device_ptr(g.flags), g.fast_tol,
+                 device_ptr(g.esq), g.nesq, device_ptr(g.mode), device_ptr(g.Xfull), device_ptr(g.gd0),
                  (int)blockIdx.x - start[p], start[p + 1] - start[p]);
 }
 
@@ -597,7 +600,8 @@ __global__ __launch_bounds__(64) void chol_panel_grouped(const CholPanelArgs* __
                                                       const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const CholPanelArgs g = a[p];
-  chol_panel_body(g.G, g.ld, g.off, g.db, g.rest, g.X, g.R, g.flags, g.mode, (int)blockIdx.x - start[p]);
+  chol_panel_body(device_ptr(g.G), g.ld, g.off, g.db, g.rest, device_ptr(g.X), device_ptr(g.R), device_ptr(g.flags),
+                  device_ptr(g.mode), (int)blockIdx.x - start[p]);
 }
 
 void chol_panel_grouped_launch(const void* args, const int* start, int count, unsigned blocks, hipStream_t s) {
@@ -647,7 +651,8 @@ __global__ __launch_bounds__(64) void chol_syrk_grouped(const CholSyrkArgs* __re
                                                      const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const CholSyrkArgs g = a[p];
-  chol_syrk_body(g.G, g.ld, g.off, g.db, g.rest, g.R, g.mode, (int)blockIdx.x - start[p]);
+  chol_syrk_body(device_ptr(g.G), g.ld, g.off, g.db, g.rest, device_ptr(g.R), device_ptr(g.mode),
+                 (int)blockIdx.x - start[p]);
 }
 
 void chol_syrk_grouped_launch(const void* args, const int* start, int count, unsigned blocks, hipStream_t s) {

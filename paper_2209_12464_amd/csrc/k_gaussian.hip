@@ -72,7 +72,8 @@ __global__ __launch_bounds__(256) void gaussian_grouped(const GaussianArgs* __re
                                                         const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const GaussianArgs g = a[p];
-  gaussian_body<T>(g.seed, g.key1, g.rows, g.cols, (T*)g.out, g.ldo, blockIdx.x - start[p], start[p + 1] - start[p]);
+  gaussian_body<T>(g.seed, g.key1, g.rows, g.cols, device_ptr((T*)g.out), g.ldo, blockIdx.x - start[p],
+                   start[p + 1] - start[p]);
 }
 
 template <typename T>
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(256) void zero_cols_grouped(const ZeroColsArgs* __r
                                                          const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const ZeroColsArgs g = a[p];
-  zero_cols_body<T>((T*)g.out, g.rows, g.c0, g.c1, g.ld, blockIdx.x - start[p], start[p + 1] - start[p]);
+  zero_cols_body<T>(device_ptr((T*)g.out), g.rows, g.c0, g.c1, g.ld, blockIdx.x - start[p], start[p + 1] - start[p]);
 }
 
 template <typename T>

@@ -285,8 +285,9 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_grouped(const GemmRecArgs* 
                                                              const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const GemmRecArgs g = a[p];
-  gemm_body<NBW, TRANS, AVEC, BVEC>((const double*)g.A, g.lda, (const double*)g.B, g.ldb, (double*)g.C, g.ldc, g.cslice,
-                                           g.M, g.N, g.K, g.kchunk, g.mtiles, g.nst, (int)blockIdx.x - start[p]);
+  gemm_body<NBW, TRANS, AVEC, BVEC>(device_ptr((const double*)g.A), g.lda, device_ptr((const double*)g.B), g.ldb,
+                                    device_ptr((double*)g.C), g.ldc, g.cslice, g.M, g.N, g.K, g.kchunk, g.mtiles,
+                                    g.nst, (int)blockIdx.x - start[p]);
 }
 
 template <int NBW, bool TRANS, bool AVEC, bool BVEC>
@@ -357,9 +358,11 @@ __global__ __launch_bounds__(256) void splitk_grouped(const SplitkArgs* __restri
   const SplitkArgs g = a[p];
   const int bid = (int)blockIdx.x - start[p], nb = start[p + 1] - start[p];
   if constexpr (V4)
-    splitk_reduce4_body((const float*)g.P, g.ldp, g.pslice, g.nsplit, (float*)g.Y, g.ldy, g.M, g.nst, bid, nb);
+    splitk_reduce4_body(device_ptr((const float*)g.P), g.ldp, g.pslice, g.nsplit, device_ptr((float*)g.Y), g.ldy, g.M,
+                        g.nst, bid, nb);
   else
-    splitk_reduce_body<T>((const T*)g.P, g.ldp, g.pslice, g.nsplit, (T*)g.Y, g.ldy, g.M, g.nst, bid, nb);
+    splitk_reduce_body<T>(device_ptr((const T*)g.P), g.ldp, g.pslice, g.nsplit, device_ptr((T*)g.Y), g.ldy, g.M, g.nst,
+                          bid, nb);
 }
 
 template <typename T, bool V4>

@@ -138,7 +138,8 @@ __global__ __launch_bounds__(256) void xsplit_grouped(const XsplitArgs* __restri
                                                       int count) {
   const int p = group_find(start, count, blockIdx.x);
   const XsplitArgs x = a[p];
-  xsplit_body(x.B, x.ldb, x.K, x.N, x.xs, x.steps, x.nblk, x.cwb, x.out, (int)blockIdx.x - start[p]);
+  xsplit_body(device_ptr(x.B), x.ldb, x.K, x.N, x.xs, x.steps, x.nblk, x.cwb, device_ptr(x.out),
+              (int)blockIdx.x - start[p]);
 }
 
 void xsplit_grouped_launch(const void* args, const int* start, int count, unsigned blocks, hipStream_t s) {
@@ -504,8 +505,9 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gemm32_grouped(const Gemm32Args
                                                                 const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const Gemm32Args x = a[p];
-  gemm32_body<NB, TRANS, WAVES>(x.A, x.lda, x.Xf, x.B, x.ldb, x.C, x.ldc, x.cslice, x.M, x.N, x.K, x.kchunk, x.mtiles,
-                                x.nst, x.xs, (int)blockIdx.x - start[p]);
+  gemm32_body<NB, TRANS, WAVES>(device_ptr(x.A), x.lda, device_ptr(x.Xf), device_ptr(x.B), x.ldb, device_ptr(x.C),
+                                x.ldc, x.cslice, x.M, x.N, x.K, x.kchunk, x.mtiles, x.nst, x.xs,
+                                (int)blockIdx.x - start[p]);
 }
 
 template <int NB, bool TRANS, int WAVES>

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(256) void gram_partial_grouped(const GramPartialArg
                                                             const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const GramPartialArgs g = a[p];
-  gram_partial_body<T, C>((const T*)g.Y, g.ldy, g.rows, g.d, g.dp, g.chunk_rows, g.npairs, g.P,
+  gram_partial_body<T, C>(device_ptr((const T*)g.Y), g.ldy, g.rows, g.d, g.dp, g.chunk_rows, g.npairs, device_ptr(g.P),
                           (int)blockIdx.x - start[p]);
 }
 
@@ -205,7 +205,8 @@ __global__ __launch_bounds__(256) void gram_reduce_grouped(const GramReduceArgs*
                                                            const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const GramReduceArgs g = a[p];
-  gram_reduce_body(g.P, g.nchunks, g.d, g.dp, g.G, g.esq, g.info, (int)blockIdx.x - start[p], start[p + 1] - start[p]);
+  gram_reduce_body(device_ptr(g.P), g.nchunks, g.d, g.dp, device_ptr(g.G), device_ptr(g.esq), device_ptr(g.info),
+                   (int)blockIdx.x - start[p], start[p + 1] - start[p]);
 }
 
 void gram_reduce_grouped_launch(const void* args, const int* start, int count, unsigned blocks, hipStream_t s) {

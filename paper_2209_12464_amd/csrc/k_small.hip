@@ -101,7 +101,8 @@ __global__ __launch_bounds__(64) void form_r_grouped(const FormRArgs* __restrict
                                                      int count) {
   const int p = group_find(start, count, blockIdx.x);
   const FormRArgs g = a[p];
-  form_r_body<T>(g.R2, g.R1, g.f1, g.f2, g.d, g.dp, (T*)g.out, g.ldo, g.transpose, (int)blockIdx.x - start[p]);
+  form_r_body<T>(device_ptr(g.R2), device_ptr(g.R1), device_ptr(g.f1), device_ptr(g.f2), g.d, g.dp,
+                 device_ptr((T*)g.out), g.ldo, g.transpose, (int)blockIdx.x - start[p]);
 }
 
 template <typename T>

@@ -159,7 +159,8 @@ __global__ __launch_bounds__(W * 64) void trinv_grouped(const TrinvRecArgs* __re
                                                         const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const TrinvRecArgs g = a[p];
-  trinv_body<W, T, AH>(g.R, g.Rinv16, g.ld, g.mode, g.X, (int)blockIdx.x - start[p]);
+  trinv_body<W, T, AH>(device_ptr(g.R), device_ptr(g.Rinv16), g.ld, device_ptr(g.mode), device_ptr(g.X),
+                       (int)blockIdx.x - start[p]);
 }
 
 template <int W, int T, int AH>

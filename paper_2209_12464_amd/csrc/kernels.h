@@ -121,8 +121,6 @@ hipError_t launch_chol(double* G, int d, int dp, double* R, double* Rinv16, int3
                        void* info, int pass_id, double fast_tol, const double* esq, int nesq,
                        int32_t* mode, double* Xfull, double* gd0, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 
-// Register-slot class (7, 14 or 17 tiles per wave) of a dp <= 256 factorization.
-int chol_slot_class(int dp);
 
 // ---- SVD of the small factor (k_svd.hip) ----
 // M (d x d, row-major, ld ldm, d <= 544) = U diag(S) V^T: S descending, U
