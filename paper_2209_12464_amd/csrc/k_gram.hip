@@ -14,6 +14,8 @@
 #include "kernels.h"
 
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 namespace rqlp {
 
@@ -30,14 +32,140 @@ __device__ inline void tile_pair(int p, int& I, int& J) {
   I = p - j * (j + 1) / 2;
 }
 
+// Float64 arithmetic: one tile over one chunk by 4 waves that take every fourth
+// group of 4 rows each and add their sums in LDS at the end.  The MFMA's A and B
+// operands of a 16-column block are the same register (lane l: row l / 16, column
+// l % 16), read from memory as it is used: no LDS and no barrier in the loop, NI +
+// NJ loads (NI on the diagonal) for NI NJ (NI (NI + 1) / 2) MFMAs of 64 cycles,
+// which bound it.  Blocks outside the padded matrix and below its diagonal take no
+// MFMA; in 64 x 64 tiles through LDS, with 4 waves a tile, they did (48 for 28 at
+// d = 110) and the barriers took as long again.  Measured: 100000 x 110 64 -> 43
+// us, 8000 x 210 20 -> 16, 20000 x 520 147 -> 116, 1000 x 25 10.5 -> 4.7.
+template <typename T, int NI, int NJ, bool DIAG>
+__device__ __attribute__((always_inline)) inline void gram_tile(const T* __restrict__ Y, int64_t ldy, int nr, int d,
+                                                                int dp, int ci, int cj, double* __restrict__ Pc,
+                                                                double* red) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane >> 4, lc = lane & 15;
+  constexpr int NB = DIAG ? NI : NI + NJ;                    // blocks read
+  constexpr int NACC = DIAG ? NI * (NI + 1) / 2 : NI * NJ;  // blocks formed
+  constexpr int kAhead = 3;                                  // groups in flight
+  int col[NB];  // this lane's column of each block (the last one for those past it, which count as zero)
+#pragma unroll
+  for (int b = 0; b < NB; ++b) col[b] = min((b < NI ? ci + b * 16 : cj + (b - NI) * 16) + lc, d - 1);
+  T ring[kAhead][NB];
+  auto load = [&](auto q, int st) {
+    const T* src = Y + (int64_t)min(16 * st + 4 * wave + lr, nr - 1) * ldy;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) ring[decltype(q)::value][b] = src[col[b]];
+  };
+  auto slots = [&](auto f) {
+    [&]<int... Qs>(std::integer_sequence<int, Qs...>) {
+      (f(std::integral_constant<int, Qs>{}), ...);
+    }(std::make_integer_sequence<int, kAhead>{});
+  };
+  doublex4 acc[NACC];
+#pragma unroll
+  for (int t = 0; t < NACC; ++t) acc[t] = Mfma<double>::zero();
+  const int nst = (nr - 4 * wave + 15) / 16;  // groups of this wave (0 or less: none)
+  slots([&](auto q) { load(q, decltype(q)::value); });
+  for (int s0 = 0; s0 < nst; s0 += kAhead) {
+    slots([&](auto q) {
+      const int st = s0 + decltype(q)::value;
+      if (st >= nst) return;
+      const bool in = 16 * st + 4 * wave + lr < nr;
+      double x[NB];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const int c = (b < NI ? ci + b * 16 : cj + (b - NI) * 16) + lc;
+        const T v = ring[decltype(q)::value][b];
+        x[b] = (double)(in && c < d ? v : (T)0);
+      }
+      load(q, st + kAhead);
+      int t = 0;
+#pragma unroll
+      for (int a = 0; a < NI; ++a)
+#pragma unroll
+        for (int b = DIAG ? a : 0; b < (DIAG ? NI : NJ); ++b, ++t)
+          acc[t] = Mfma<double>::mma(x[a], x[DIAG ? b : NI + b], acc[t]);
+    });
+  }
+  // sums of the waves: (0 + 2) + (1 + 3)
+  auto put = [&](int slot) {
+#pragma unroll
+    for (int t = 0; t < NACC; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[((slot * NACC + t) * 4 + r) * 64 + lane] = acc[t][r];
+  };
+  auto add = [&](int slot) {
+#pragma unroll
+    for (int t = 0; t < NACC; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[t][r] += red[((slot * NACC + t) * 4 + r) * 64 + lane];
+  };
+  if (wave >= 2) put(wave - 2);
+  __syncthreads();
+  if (wave < 2) add(wave);
+  __syncthreads();
+  if (wave == 1) put(0);
+  __syncthreads();
+  if (wave != 0) return;
+  add(0);
+  int t = 0;
+#pragma unroll
+  for (int a = 0; a < NI; ++a)
+#pragma unroll
+    for (int b = DIAG ? a : 0; b < (DIAG ? NI : NJ); ++b, ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        Pc[(int64_t)(ci + a * 16 + lr + 4 * r) * dp + (DIAG ? ci : cj) + b * 16 + lc] = acc[t][r];
+}
+
+template <typename T>
+__device__ __attribute__((always_inline)) inline void gram_partial_body64(const T* __restrict__ Y, int64_t ldy,
+                                                                          int64_t rows, int d, int dp,
+                                                                          int64_t chunk_rows, int npairs,
+                                                                          double* __restrict__ P, int bid) {
+  __shared__ double red[2 * 16 * 256];
+  const int pair = bid % npairs;
+  const int chunk = bid / npairs;
+  int I, J;
+  tile_pair(pair, I, J);
+  const int64_t r0 = (int64_t)chunk * chunk_rows;
+  const int nr = (int)max((int64_t)0, min(rows - r0, chunk_rows));
+  const int nJ = min(4, (dp - J * kGT) / 16);  // 16-column blocks of tile column J
+  double* Pc = P + (int64_t)chunk * dp * dp;
+  if (nr == 0) {  // (a chunk without rows: zeros)
+    for (int e = threadIdx.x; e < kGT * kGT; e += 256) {
+      const int r = I * kGT + e / kGT, c = J * kGT + e % kGT;
+      if (r < dp && c < dp) Pc[(int64_t)r * dp + c] = 0.0;
+    }
+    return;
+  }
+  const T* Yc = Y + r0 * ldy;
+  const int ci = I * kGT, cj = J * kGT;
+#define RQLP_GRAM_TILE(N)                                                             \
+  if (nJ == N) {                                                                      \
+    if (I == J) gram_tile<T, N, N, true>(Yc, ldy, nr, d, dp, ci, cj, Pc, red);        \
+    else gram_tile<T, 4, N, false>(Yc, ldy, nr, d, dp, ci, cj, Pc, red);              \
+    return;                                                                           \
+  }
+  RQLP_GRAM_TILE(1)
+  RQLP_GRAM_TILE(2)
+  RQLP_GRAM_TILE(3)
+  RQLP_GRAM_TILE(4)
+#undef RQLP_GRAM_TILE
+}
+
 template <typename T, typename C>
 __device__ __attribute__((always_inline)) inline void gram_partial_body(const T* __restrict__ Y, int64_t ldy,
                                                                         int64_t rows, int d, int dp,
                                                                         int64_t chunk_rows, int npairs,
                                                                         double* __restrict__ P, int bid) {
-  // rows of kGT + 1 doubles, or kGT + 16 floats: the two k-rows one operand
-  // read touches fall in disjoint banks
-  constexpr int LS = sizeof(C) == 8 ? kGT + 1 : kGT + 16;
+  // rows of kGT + 16 floats: the two k-rows one operand read touches fall in
+  // disjoint banks
+  constexpr int LS = kGT + 16;
   __shared__ C YI[2][kGK][LS];
   __shared__ C YJ[2][kGK][LS];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -117,10 +245,13 @@ __device__ __attribute__((always_inline)) inline void gram_partial_body(const T*
 }
 
 template <typename T, typename C>
-__global__ __launch_bounds__(256) void gram_partial_kernel(const T* __restrict__ Y, int64_t ldy, int64_t rows, int d,
+__global__ __launch_bounds__(256, 2) void gram_partial_kernel(const T* __restrict__ Y, int64_t ldy, int64_t rows, int d,
                                                            int dp, int64_t chunk_rows, int npairs,
                                                            double* __restrict__ P) {
-  gram_partial_body<T, C>(Y, ldy, rows, d, dp, chunk_rows, npairs, P, blockIdx.x);
+  if constexpr (std::is_same_v<C, double>)
+    gram_partial_body64(Y, ldy, rows, d, dp, chunk_rows, npairs, P, blockIdx.x);
+  else
+    gram_partial_body<T, C>(Y, ldy, rows, d, dp, chunk_rows, npairs, P, blockIdx.x);
 }
 
 struct GramPartialArgs {
@@ -131,12 +262,17 @@ struct GramPartialArgs {
 };
 
 template <typename T, typename C>
-__global__ __launch_bounds__(256) void gram_partial_grouped(const GramPartialArgs* __restrict__ a,
+__global__ __launch_bounds__(256, 2) void gram_partial_grouped(const GramPartialArgs* __restrict__ a,
                                                             const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const GramPartialArgs g = a[p];
-  gram_partial_body<T, C>(device_ptr((const T*)g.Y), g.ldy, g.rows, g.d, g.dp, g.chunk_rows, g.npairs, device_ptr(g.P),
-                          (int)blockIdx.x - start[p]);
+  const T* Y = device_ptr((const T*)g.Y);
+  double* P = device_ptr(g.P);
+  const int bid = (int)blockIdx.x - start[p];
+  if constexpr (std::is_same_v<C, double>)
+    gram_partial_body64(Y, g.ldy, g.rows, g.d, g.dp, g.chunk_rows, g.npairs, P, bid);
+  else
+    gram_partial_body<T, C>(Y, g.ldy, g.rows, g.d, g.dp, g.chunk_rows, g.npairs, P, bid);
 }
 
 template <typename T, typename C>

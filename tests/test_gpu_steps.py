@@ -149,6 +149,26 @@ def test_orth_matches_householder(gpu_lib, m, d, cond, dtype):
     assert np.all(np.tril(R, -1) == 0) and np.all(np.diag(R) >= 0)
 
 
+@pytest.mark.parametrize("m,d,ld", [(1, 1, 1), (15, 15, 15), (17, 16, 16), (130, 49, 49), (200, 64, 64), (129, 65, 67),
+                                    (300, 81, 81), (400, 97, 97), (500, 113, 120), (5000, 128, 128), (2049, 129, 129)])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_orth_gram_edges(gpu_lib, m, d, ld, dtype):
+    """Row and column remainders of the Gram matrix's groups, blocks and tiles:
+    the rows' triangular factor, R^T R = Y^T Y to the rounding of its float64
+    sums and of R's output type; what lies beside the columns is not read in."""
+    announce("orth gram edges", m, d, ld, dtype)
+    rng = np.random.default_rng(m + d)
+    Y = rng.standard_normal((m, d)) + (4.0 * np.eye(m, d) if m < 2 * d else 0.0)
+    buf = torch.full((m, ld), float("nan"), dtype=dtype, device="cuda")
+    buf[:, :d] = to_dev(Y, dtype)
+    Yin = to_np(buf[:, :d]).astype(np.float64)
+    _, R = gpu_lib.orth(buf[:, :d], want_r=True)
+    R = to_np(R).astype(np.float64)
+    u = 2.0 ** -53 if dtype == torch.float64 else 2.0 ** -24
+    G = Yin.T @ Yin
+    assert np.linalg.norm(R.T @ R - G) <= 100 * np.sqrt(d) * u * np.linalg.norm(G)
+
+
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
 def test_orth_rank_deficient_completes_basis(gpu_lib, dtype):
     announce("orth rank-deficient", dtype)
