@@ -197,10 +197,11 @@ GemmArgs<T> plan_gemm(int trans, const T* A, int64_t lda, const T* B, int64_t ld
   // Resident workgroup slots: two 4-wave workgroups per CU (register
   // limited), 256 CUs.  Split K so that all slabs x splits fit in one round.
   const int target = std::max(1, env_int("RQLP_GEMM_TARGET_WGS", 512));
-  // at least 512 reduction steps per split: a small product is not cut into
-  // many slivers (a batch of them fills the GPU anyway), a large one still
-  // takes about two workgroups per CU
-  const int64_t kmin = std::max(16, env_int("RQLP_GEMM_MIN_KCHUNK", 512));
+  // at least 256 reduction steps per split (what splitk_cap allows): a small
+  // product is a chain of 16-wide steps of about 1.3 us each, twice as long with
+  // parts of 512 (1000 x 800 x 25: 33 and 42 us for the two products, 19 and
+  // 23 with 256); a large one still takes about two workgroups per CU
+  const int64_t kmin = std::max(16, env_int("RQLP_GEMM_MIN_KCHUNK", 256));
   int64_t ns = target / g.mtiles;
   ns = std::min<int64_t>(ns, std::max<int64_t>(1, ceil_div(K, kmin)));
   ns = std::max<int64_t>(1, ns);
