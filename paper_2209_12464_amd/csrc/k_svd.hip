@@ -31,7 +31,7 @@
 // to a block (half the steps of 8, at the same number of rounds), rounds that
 // touch 32 x 32 values in LDS instead of 2 dp x 32 (about 860 cycles each, with
 // one barrier, against a reduction over a column and its update), the angles
-// from the hardware's estimates, J's accumulation one round behind on waves of
+// from the hardware's estimates and one Newton step, J's accumulation one round behind on waves of
 // its own, and V's product one step behind on workgroups of its own.  At d = 210
 // (10 sweeps of 13 steps) a step takes 35 thousand cycles: load 4, G 6, rounds 14,
 // X J 5, barrier 5.  All sweeps run in one cooperative launch.  Measured against
@@ -124,10 +124,11 @@ __device__ __forceinline__ bool svd_needs(double a, double b, double d, double i
 // The rotation x_u <- c x_u - s x_v, x_v <- s x_u + c x_v that does it: with h =
 // d - a and r = sqrt(h^2 + 4 b^2), t = 2 sign(h) b / (|h| + r) (the t above),
 // c = 1 / sqrt(1 + t^2), s = c t; c = 1, s = 0 where none is needed.  t is taken
-// from the hardware estimates (relative error about 2^-23): any t gives an
-// exact rotation, and this one leaves 2^-22 of b where an exact one leaves
-// rounding errors, less than what the rotations of the other columns bring
-// back.  c has full accuracy.  Values whose squares leave the range are scaled
+// from the hardware estimates (relative error about 2^-23) with one Newton step on
+// b t^2 + h t - b = 0, whose derivative at the root is +-r: three FMAs, an error of
+// 2^-44.  (Without it the last rotations leave 2^-22 of b, up to the bound of
+// svd_needs, and nearby singular vectors are that much less accurate.)  c has full
+// accuracy.  Values whose squares leave the range are scaled
 // first (a whole wave at once; rare).
 __device__ __forceinline__ void svd_rotation(double a, double b, double d, double itol, double& c, double& s) {
   double h = d - a, b2 = b + b;
@@ -139,8 +140,10 @@ __device__ __forceinline__ void svd_rotation(double a, double b, double d, doubl
     b2 = __builtin_amdgcn_ldexp(b2, e);
     x = fma(b2, b2, h * h);
   }
-  const double r = fma(x, __builtin_amdgcn_rsq(x), fabs(h));
-  const double t = (h < 0.0 ? -b2 : b2) * __builtin_amdgcn_rcp(r);
+  const double y = __builtin_amdgcn_rsq(x), hb = 0.5 * b2;
+  const double t0 = (h < 0.0 ? -b2 : b2) * __builtin_amdgcn_rcp(fma(x, y, fabs(h)));
+  const double f = fma(fma(hb, t0, h), t0, -hb);
+  const double t = fma(h < 0.0 ? f : -f, y, t0);
   const double z = rsqrt_nr(fma(t, t, 1.0));
   c = rot ? z : 1.0;
   s = rot ? z * t : 0.0;
