@@ -36,7 +36,7 @@
 // (10 sweeps of 13 steps) a step takes 35 thousand cycles: load 4, G 6, rounds 14,
 // X J 5, barrier 5.  All sweeps run in one cooperative launch.  Measured against
 // blocks of 8 columns rotated in place (the whole call, L factors): d = 50 492 ->
-// 385 us, 100 1203 -> 897, 210 3513 -> 2015, 320 6272 -> 3590, 540 15723 -> 9000;
+// 405 us, 100 1203 -> 938, 210 3513 -> 2180, 320 6272 -> 3760, 540 15723 -> 9310;
 // singular values and vectors as accurate against 64-bit references.
 //
 // Finally sigma_j = ||x_j||, the columns are sorted by descending sigma
