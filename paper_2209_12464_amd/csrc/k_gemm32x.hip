@@ -6,22 +6,26 @@
 // leave), and a product a x is taken as the six partial products
 //     a_l x_h + a_h x_l + a_m x_m + a_m x_h + a_h x_m + a_h x_h,
 // each exact in float32, accumulated in float32.  The three products left out
-// (m l, l m, l l) are below 2^-25 of a x, a quarter of float32's own rounding
-// of it, and a 32x32x16 MFMA adds 16 products into its accumulator at a time,
-// so that a dot product sees fewer roundings than with the float32 MFMA.
-// bfloat16 has float32's range, so no scales are needed; six bfloat16 MFMAs
-// have 16/6 = 2.7 times the rate of the float32 MFMA.  Measured, one product
+// (m l, l m, l l) are below 2^-24 of a x together, float32's own rounding of it,
+// and a 32x32x16 MFMA adds 16 products into its accumulator at a time, so that a
+// dot product sees fewer roundings than with the float32 MFMA.
+// bfloat16 has float32's range, so one constant factor serves; six bfloat16
+// MFMAs have 16/6 = 2.7 times the rate of the float32 MFMA.  Measured, one product
 // with its split-K reduction: 6000 x 3000 x 110: 41 us (float32 MFMA 92), 8000
 // x 8000 x 210: 163 us (320), where it is the chip's power that binds (the
 // clock falls to 2.0 GHz, 1.8 at 20000 x 15000; 1.05-1.17 PFLOP/s of bfloat16,
 // what the vendor's large matrix products reach here); relative error against
 // float64 at 6000 x 3000 x 110 3.9e-7 (float32 MFMA 4.1e-7).
 //
-// What the parts cannot represent is left to float32: an output that is not
-// finite (a part of an infinity or of a value that rounds up to one) or is
-// nonzero below 2^-96 (the last part of inputs below 2^-110 falls under
-// bfloat16's smallest denormal) sends its wave's 32 rows through the float32
-// MFMA again, straight from the inputs.
+// Range: the parts are multiples of 2^-133, bfloat16's smallest denormal, and
+// float32's values of 2^-149.  Both operands are therefore multiplied by 2^16, so
+// that every value is the sum of its parts, and the sums by 2^-32.  What leaves the
+// range on the way (values from 2^112, sums from 2^96) or is not finite shows as an
+// output that is not finite, and sends its wave's 32 rows through the float32 MFMA
+// again, straight from the inputs.  (Without the factors small values lose parts,
+// and a guard on the size of the outputs either misses them, where the other
+// operand is large, or redoes the far parts of a split reduction over a matrix that
+// decays: a 4000 x 3000 Gaussian kernel times 110 columns took 200 us, now 35 us.)
 //
 // Tiles as in k_gemm32.hip, but X is split by each workgroup on its way to
 // LDS (once per reduction step, stored as whole operand fragments, double
@@ -43,6 +47,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kBK = 32;
+constexpr float kLift = 0x1p16f;
 
 // two floats to packed bfloat16, round to nearest even
 __device__ inline uint32_t pk_bf16(float a, float b) {
@@ -50,11 +55,10 @@ __device__ inline uint32_t pk_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// The three parts of a pair of values, packed (exact for finite values of at
-// least 2^-110).
+// The three parts of a pair of values times kLift, packed.
 __device__ inline void split3(float x0, float x1, uint32_t* part) {
-  const uint32_t h = pk_bf16(x0, x1);
-  const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
+  const uint32_t h = pk_bf16(x0 * kLift, x1 * kLift);
+  const float r0 = fmaf(x0, kLift, -__uint_as_float(h << 16)), r1 = fmaf(x1, kLift, -__uint_as_float(h & 0xffff0000u));
   const uint32_t m = pk_bf16(r0, r1);
   part[0] = h;
   part[1] = m;
@@ -263,22 +267,30 @@ __device__ __attribute__((always_inline)) inline void gemm32x_body(
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const float v = fabsf(acc[nb][r]);
-      bad |= !(v < __builtin_inff()) || (v < 0x1p-96f && v != 0.f);
+      bad |= !(fabsf(acc[nb][r]) < __builtin_inff());
+      acc[nb][r] *= 1.f / (kLift * kLift);
     }
   if (__any(bad)) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[nb] = (floatx16)0.0f;
-    for (int k0 = kbeg; k0 < kend; k0 += 2) {
-      const int k = k0 + g;
-      const bool kin = k < kend;
-      const float a = kin ? A[TRANS ? (int64_t)k * lda + arow : (int64_t)arow * lda + k] : 0.f;
+    constexpr int kRun = 4;  // pairs of reduction indices loaded together
+    for (int k0 = kbeg; k0 < kend; k0 += 2 * kRun) {
+      float a[kRun], x[kRun][NB];
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const int n = nb * 32 + lc;
-        const float x = (kin && n < N) ? B[(int64_t)k * ldb + n] : 0.f;
-        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, x, acc[nb], 0, 0, 0);
+      for (int i = 0; i < kRun; ++i) {
+        const int k = k0 + 2 * i + g;
+        const bool kin = k < kend;
+        a[i] = kin ? A[TRANS ? (int64_t)k * lda + arow : (int64_t)arow * lda + k] : 0.f;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          const int n = nb * 32 + lc;
+          x[i][nb] = (kin && n < N) ? B[(int64_t)k * ldb + n] : 0.f;
+        }
       }
+#pragma unroll
+      for (int i = 0; i < kRun; ++i)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], x[i][nb], acc[nb], 0, 0, 0);
     }
   }
 

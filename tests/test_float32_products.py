@@ -1,0 +1,113 @@
+"""Float32 products as products of three bfloat16 parts: the split on the CPU (its
+exactness and what the products that are left out amount to), and on the GPU the
+product by itself at the edges of both row tiles and with operands whose parts
+leave bfloat16's range."""
+import numpy as np
+import pytest
+
+from oracle.bf16 import round_bf16
+from tests.gpu_util import announce, to_dev
+
+U = 2.0 ** -24  # unit roundoff of float32
+
+
+def _parts(x):
+    """The three bfloat16 parts of float32 values (as float64)."""
+    x = x.astype(np.float64)
+    h = round_bf16(x.astype(np.float32)).astype(np.float64)
+    m = round_bf16((x - h).astype(np.float32)).astype(np.float64)
+    low = round_bf16((x - h - m).astype(np.float32)).astype(np.float64)
+    return h, m, low
+
+
+def test_three_parts_are_exact():
+    """h + m + l is the value itself for every float32 value below 2^111 times 2^16;
+    the three products of parts left out are within 2^-24 of a product (the rounding
+    that float32 gives it)."""
+    rng = np.random.default_rng(4)
+    x = (rng.uniform(1, 2, 200000) * 2.0 ** rng.integers(-149, 111, 200000)).astype(np.float32)
+    lifted = (x.astype(np.float64) * 2.0 ** 16).astype(np.float32)
+    assert np.array_equal(sum(_parts(lifted)), lifted.astype(np.float64))
+    a, b = (rng.uniform(1, 2, 200000).astype(np.float32) for _ in range(2))
+    (_, am, al), (_, bm, bl) = _parts(a), _parts(b)
+    left = np.abs(am * bl + al * bm + al * bl)
+    assert np.max(left / (a.astype(np.float64) * b)) <= 2.0 ** -24
+
+
+def _gemm(gpu_lib, A, X, trans):
+    import torch
+    Y = gpu_lib.gemm(to_dev(A), to_dev(X), trans=trans)
+    torch.cuda.synchronize()
+    return Y.cpu().numpy()
+
+
+def _ref(A, X, trans):
+    A64, X64 = (A.T if trans else A).astype(np.float64), X.astype(np.float64)
+    return A64 @ X64, np.abs(A64) @ np.abs(X64)
+
+
+# the 256-row tile in both directions: remainders of rows, reduction steps and
+# column blocks, one column pass and two; the 128-row tile next to its limits
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,d", [(6401, 1103, 97), (6401, 1103, 280), (6401, 1103, 289), (6145, 1024, 32),
+                                   (6144, 1024, 33), (6401, 1023, 64)])
+@pytest.mark.parametrize("trans", [False, True])
+def test_gemm_row_tiles(gpu_lib, m, n, d, trans):
+    announce("float32 gemm tiles", m, n, d, trans)
+    rng = np.random.default_rng(m + n + d)
+    A = rng.standard_normal((n, m) if trans else (m, n)).astype(np.float32)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    ref, bound = _ref(A, X, trans)
+    assert np.all(np.abs(_gemm(gpu_lib, A, X, trans) - ref) <= 2 * n * U * bound)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("trans", [False, True])
+@pytest.mark.parametrize("ea,ex", [(-118, 98), (-125, 100), (98, -118), (100, -125), (-118, 0), (0, -118),
+                                   (-125, 127), (127, -126)])
+@pytest.mark.parametrize("where", ["all", "some"])
+def test_gemm_small_operands(gpu_lib, trans, ea, ex, where):
+    """Operands whose parts would fall under bfloat16's smallest denormal, against
+    large ones: every result an ordinary float32, as accurate as any.  "some": only
+    every fifth reduction index holds them, beside operands near 1."""
+    announce("float32 gemm small operands", trans, ea, ex, where)
+    rng = np.random.default_rng(ea + 200)
+    m, k, d = 75, 83, 40
+    A, X = rng.uniform(1, 1.9, (m, k)), rng.uniform(1, 1.9, (k, d)) * rng.choice([-1, 1], (k, d))
+    if where == "all":
+        X = np.abs(X)  # (no cancellation)
+        A, X = A * 2.0 ** (ea - 7 * (ea > ex)), X * 2.0 ** (ex - 7 * (ex > ea))  # (sums within range)
+    else:
+        A[:, ::5] *= 2.0 ** ea
+        X[::5] *= 2.0 ** ex
+    A, X = A.astype(np.float32), X.astype(np.float32)
+    A = np.ascontiguousarray(A.T) if trans else A
+    ref, bound = _ref(A, X, trans)
+    assert np.all(np.abs(_gemm(gpu_lib, A, X, trans) - ref) <= 2 * k * U * bound)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("trans", [False, True])
+def test_gemm_range_ends(gpu_lib, trans):
+    """Values that round up to an infinity in bfloat16, and infinities and values
+    that are no number, which reach their own rows and columns only."""
+    announce("float32 gemm range ends", trans)
+    rng = np.random.default_rng(8)
+    m, k, d = 75, 83, 40
+    top = np.float32(np.finfo(np.float32).max)
+    A, X = rng.standard_normal((m, k)).astype(np.float32), (rng.standard_normal((k, d)) / 64).astype(np.float32)
+    A[5, 7] = top
+    ref, bound = _ref(A, X, False)
+    At = np.ascontiguousarray(A.T) if trans else A
+    assert np.all(np.abs(_gemm(gpu_lib, At, X, trans) - ref) <= 2 * k * U * bound)
+    A[9, 80], A[40, 3], X[50, 6] = np.inf, np.nan, -np.inf
+    At = np.ascontiguousarray(A.T) if trans else A
+    Y = _gemm(gpu_lib, At, X, trans)
+    with np.errstate(invalid="ignore"):
+        ref = A.astype(np.float64) @ X.astype(np.float64)
+    fine = np.ones((m, d), bool)
+    fine[[9, 40]] = False
+    fine[:, 6] = False
+    assert np.array_equal(np.isnan(Y), np.isnan(ref)) and np.array_equal(np.isinf(Y), np.isinf(ref))
+    assert np.array_equal(np.sign(Y[np.isinf(ref)]), np.sign(ref[np.isinf(ref)]))
+    assert np.all(np.abs(Y[fine] - ref[fine]) <= 2 * k * U * bound[fine])
