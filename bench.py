@@ -29,8 +29,8 @@ sys.path.insert(0, ROOT)
 PEAK = {  # MI355X published dense peaks
     "bf16_mfma_tflops": 2500.0,
     "f32_mfma_tflops": 157.3,
-    # float32 products run as three float16 partial products each
-    "f32_split_tflops": 2500.0 / 3.0,
+    # float32 products run as six bfloat16 partial products each
+    "f32_split_tflops": 2500.0 / 6.0,
     "f64_mfma_tflops": 78.6,
     "hbm_gbs": 8000.0,
 }
@@ -339,7 +339,7 @@ def run_serve_bench(args, w, rqlp, torch, dev):
 
 def products_roofline(rqlp, ctx, As, reqs, q, torch):
     """Products with A of the given problems, event-timed one problem after
-    another: achieved TFLOP/s against a third of the float16 MFMA peak (three
+    another: achieved TFLOP/s against a sixth of the bfloat16 MFMA peak (six
     partial products per float32 product)."""
     ctx.set_timing(True, classes=["gemm_nn", "gemm_tn"])
     for A, r in zip(As, reqs):

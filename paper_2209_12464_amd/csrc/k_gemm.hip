@@ -425,15 +425,15 @@ static void dispatch_nb(const GemmArgs<double>& g, hipStream_t s, int grid, doub
   }
 }
 
-// The main kernel of one column pass (from column c0).
-static void launch_pass(const GemmArgs<double>& g, int, int grid, double* C, int64_t ldc, int64_t cslice, int nst,
+// The main kernel of one column pass.
+static void launch_pass(const GemmArgs<double>& g, int grid, double* C, int64_t ldc, int64_t cslice, int nst,
                         hipStream_t s) {
   if (g.trans) dispatch_nb<true>(g, s, grid, C, ldc, cslice, nst);
   else dispatch_nb<false>(g, s, grid, C, ldc, cslice, nst);
 }
-static void launch_pass(const GemmArgs<float>& g, int c0, int grid, float* C, int64_t ldc, int64_t cslice, int nst,
+static void launch_pass(const GemmArgs<float>& g, int grid, float* C, int64_t ldc, int64_t cslice, int nst,
                         hipStream_t s) {
-  launch_gemm32_tiles(g, c0, grid, C, ldc, cslice, nst, s);
+  launch_gemm32_tiles(g, grid, C, ldc, cslice, nst, s);
 }
 
 template <typename T>
@@ -448,7 +448,8 @@ template int gemm_block_cols<double>(int);
 
 // Widest column tile of one pass; wider outputs are cut into equal passes
 // of at most this many columns (A is then streamed once per pass).
-template <typename T> constexpr int kGemmMaxCols = sizeof(T) == 4 ? 288 : 256;
+static int max_cols(const GemmArgs<double>&) { return 256; }
+static int max_cols(const GemmArgs<float>& g) { return gemm32_max_cols(g); }
 
 // Launch the main kernel (into C directly when nsplit == 1, else into the
 // partial buffer P) once per column pass and, for nsplit > 1, the ordered
@@ -458,19 +459,17 @@ hipError_t launch_gemm(GemmArgs<T> g, T* Y, int64_t ldy, int nst, T* P, hipStrea
                        hipEvent_t ev0, hipEvent_t ev1) {
   if (g.M <= 0 || nst <= 0) return hipSuccess;
   const int grid = g.mtiles * g.nsplit;
-  const int npass = (int)ceil_div(round_up(g.N, 32), kGemmMaxCols<T>);
+  const int npass = (int)ceil_div(round_up(g.N, 32), max_cols(g));
   const int cw = (int)round_up(ceil_div(g.N, npass), 32);
   if (ev0) (void)hipEventRecord(ev0, s);
-  if constexpr (sizeof(T) == 4)
-    if (g.xsplit) launch_xsplit(g, cw, s);
   for (int c0 = 0; c0 < g.N; c0 += cw) {
     GemmArgs<T> gc = g;
     gc.B = g.B + c0;
     gc.N = std::min(cw, g.N - c0);
     // the last pass also writes the zero columns [N, nst)
     const int nst_c = (c0 + cw >= g.N) ? nst - c0 : cw;
-    if (g.nsplit == 1) launch_pass(gc, c0, grid, Y + c0, ldy, 0, nst_c, s);
-    else launch_pass(gc, c0, grid, P + c0, (int64_t)nst, (int64_t)g.M * nst, nst_c, s);
+    if (g.nsplit == 1) launch_pass(gc, grid, Y + c0, ldy, 0, nst_c, s);
+    else launch_pass(gc, grid, P + c0, (int64_t)nst, (int64_t)g.M * nst, nst_c, s);
   }
   if (g.nsplit > 1) splitk_dispatch<T>(P, g.nsplit, g.M, nst, Y, ldy, s);
   // the timed interval covers the product and its split-K reduction

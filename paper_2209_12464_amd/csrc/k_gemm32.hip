@@ -1,51 +1,58 @@
-// Dense float32 products with A, Y = A X (NN) and Y = A^T X (TN), on the
-// float16 matrix cores: the sketch, power-step and projection products of
-// Algorithms 1 and 2, whose X is a Gaussian test matrix or a basis.
+// Dense float32 products with A, Y = A X (NN) and Y = A^T X (TN), on the bfloat16
+// matrix cores: the sketch, power-step and projection products of Algorithms 1 and
+// 2 and rqlp_gemm.
 //
-// Every value is scaled by a power of two and split into two float16 parts,
-// x s = h + l (11 + 11 significand bits and the sign of l: within half an ulp
-// of float32, rms 2^-24.6 of x), and a product is taken as the three partial
-// products a_l x_h + a_h x_l + a_h x_h, each exact in float32, accumulated in
-// float32; the fourth, a_l x_l, is 2^-24.8 of a x (rms).  A 32x32x16 MFMA adds
-// 16 products into its accumulator at a time, so a dot product sees fewer
-// roundings than with the float32 MFMA, which dominate both: the relative
-// error against float64 at 8000 x 8000 x 210 is 3.7e-7, with the float32
-// MFMA 5.7e-7.  Three float16 MFMAs have 16/3 = 5.3 times the rate of the
-// float32 MFMA.
+// Each float is split exactly into three bfloat16 parts, x = h + m + l (8 + 8
+// + 8 significand bits, each part the rounding of what the parts before it
+// leave), and a product a x is taken as the six partial products
+//     a_l x_h + a_h x_l + a_m x_m + a_m x_h + a_h x_m + a_h x_h,
+// each exact in float32, accumulated in float32.  The three products left out
+// (m l, l m, l l) are below 2^-24 of a x together, float32's own rounding of it,
+// and a 32x32x16 MFMA adds 16 products into its accumulator at a time, so that a
+// dot product sees fewer roundings than with the float32 MFMA.
+// bfloat16 has float32's range, so one constant factor serves; six bfloat16
+// MFMAs have 16/6 = 2.7 times the rate of the float32 MFMA.  Measured, one product
+// with its split-K reduction: 6000 x 3000 x 110: 41 us (float32 MFMA 92), 8000
+// x 8000 x 210: 163 us (320), where it is the chip's power that binds (the
+// clock falls to 2.0 GHz, 1.8 at 20000 x 15000; 1.05-1.17 PFLOP/s of bfloat16,
+// what the vendor's large matrix products reach here); relative error against
+// float64 at 6000 x 3000 x 110 3.9e-7 (float32 MFMA 4.1e-7).
 //
-// Range: X is scaled by the caller's power of two (g.xscale), A by one of its
-// own per row of op(A), taken from the first reduction step and lowered when
-// a later value asks for it (what was accumulated follows), so that the
-// largest value of a row so far lies in [2^7, 2^15) and float16's smallest
-// step is at most 2^-31 of it.  What is left to float32: an output that is
-// not finite (a part of an infinity, or of an X value past the range) or is
-// nonzero below 2^-96 (inputs whose parts no scale of float32's range can
-// hold) sends its wave's 32 rows through the float32 MFMA again, straight from
-// the inputs.
+// Range: the parts are multiples of 2^-133, bfloat16's smallest denormal, and
+// float32's values of 2^-149.  Both operands are therefore multiplied by 2^16, so
+// that every value is the sum of its parts, and the sums by 2^-32.  What leaves the
+// range on the way (values from 2^112, sums from 2^96) or is not finite shows as an
+// output that is not finite, and sends its wave's 32 rows through the float32 MFMA
+// again, straight from the inputs.  (Without the factors small values lose parts,
+// and a guard on the size of the outputs either misses them, where the other
+// operand is large, or redoes the far parts of a split reduction over a matrix that
+// decays: a 4000 x 3000 Gaussian kernel times 110 columns took 200 us, now 35 us.)
 //
-// Tiles: a workgroup owns 32 WAVES rows (256 or 128) and up to 288 columns of
-// Y; wave w the rows 32 w .. and every column, as NB blocks of 32 x 32.  So
-// each value of A is loaded, split and used by one wave only: A goes from
-// memory straight to the registers of its MFMA operands (two reduction steps
-// of 32 ahead), split while the other half step's MFMAs run, and only X passes
-// through LDS.  X is split once per product by a kernel of its own, into whole
-// operand fragments in the order the product reads them, so that a step's
-// tile is one contiguous run copied straight to LDS (a ring of three stages,
-// two steps ahead, one barrier per step) and read back without bank
-// conflicts.  The reduction is split over workgroups (split-K) and the partial
-// slabs are summed in a fixed order; an output's summation order depends on
-// the split only, not on the row tile.
+// Tiles: a workgroup owns 32 WAVES rows (256 or 128) and up to 288 columns of Y;
+// wave w the rows 32 w .. and every column, as NB blocks of 32 x 32.  So each value
+// of A is loaded, split and used by one wave only, and goes from memory straight to
+// the registers of its MFMA operands, split while the other half step's MFMAs run.
+// X is split by the workgroup on its way to LDS (once per reduction step, stored as
+// whole operand fragments, double buffered) and read back without bank conflicts.
+// The reduction is split over workgroups (split-K) and the partial slabs are summed
+// in a fixed order; an output's summation order depends on the split only, not on
+// the row tile.
 //
-// Measured, one product with X's split (4-5 us) and the split-K reduction
-// (10 us at 8000 x 224): 8000 x 8000 x 210 112 us (float32 MFMA 268 / 288),
-// 20000 x 15000 x 224 424 us, 6000 x 3000 x 110 36 us (65), 2700 x 2700 x 288
-// 40 us (90).  At 8000 x 8000 the main kernel takes 98 us; the MFMAs alone are
-// 40, A's 256 MB at the card's copy rate 50; what is left is the latency
-// between a step's parts (without any global load it still takes 82 us: LDS
-// reads, conversions and one barrier per step) and the partial slabs' 57 MB.
-// Tried on the way: X split by each workgroup on its way to LDS, no separate
-// kernel (125-141 us); X tiles and A one step ahead (122); X's fragments read
-// one block ahead of their products (122).
+// BLOCKED (decompositions): the six partial products of 16 reduction indices are
+// summed by themselves and the sum is added to the accumulator, one rounding of it
+// in the place of six: relative error against float64 2.5e-7 instead of 5.1e-7 at
+// 8000 x 8000 x 210, 2.1e-7 instead of 3.9e-7 at 6000 x 3000 x 110, for 5 to 10 %
+// more time (168 -> 180 us, 41 -> 46 us; 2700 x 2700 x 270 46 -> 51).  What several
+// products, and the orthonormalizations between them, make of their rounding errors
+// adds up; a product by itself (rqlp_gemm) is as accurate as on the float32 MFMA
+// without.  The additions stand between the MFMAs of the next block (after them:
+// another 5 %) and take a second block's worth of registers, so that with eight
+// waves 224 columns are the most (8000 x 8000 x 256: 225 us in two passes, 270 in
+// one that spills).
+//
+// Two float16 parts of each operand and three products, with a scale for each row of
+// A, took 112 us at 8000 x 8000 x 210, but held 22 to 23 bits of a value (fewer of
+// one far below its row's largest) where float32 has 24, and L's errors grew by it.
 #include "common.h"
 #include "grouped.h"
 #include "kernels.h"
@@ -56,122 +63,52 @@ namespace rqlp {
 
 namespace {
 
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // four floats at any float's alignment (the target takes unaligned vector loads)
 typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef __attribute__((address_space(3))) void* lds_ptr;
 
-constexpr int kBK = 32;      // reduction step
+constexpr int kBK = 32;
+constexpr float kLift = 0x1p16f;
 
-// A pair of values times s as two packed float16 parts.
-__device__ inline void split2(float x0, float x1, float s, uint32_t& hi, uint32_t& lo) {
-  const f16x2 h = {(_Float16)(x0 * s), (_Float16)(x1 * s)};
-  const f16x2 l = {(_Float16)fmaf(x0, s, -(float)h.x), (_Float16)fmaf(x1, s, -(float)h.y)};
-  hi = __builtin_bit_cast(uint32_t, h);
-  lo = __builtin_bit_cast(uint32_t, l);
+// two floats to packed bfloat16, round to nearest even
+__device__ inline uint32_t pk_bf16(float a, float b) {
+  const floatx2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+// The three parts of a pair of values times kLift, packed.
+__device__ inline void split3(float x0, float x1, uint32_t* part) {
+  const uint32_t h = pk_bf16(x0 * kLift, x1 * kLift);
+  const float r0 = fmaf(x0, kLift, -__uint_as_float(h << 16)), r1 = fmaf(x1, kLift, -__uint_as_float(h & 0xffff0000u));
+  const uint32_t m = pk_bf16(r0, r1);
+  part[0] = h;
+  part[1] = m;
+  part[2] = pk_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
 }
 
 __device__ inline floatx16 mma(u32x4 a, u32x4 b, floatx16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0,
+                                                 0);
 }
-
-// 2^e for -126 <= e <= 127
-__device__ inline float pow2(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }
-
-// s_waitcnt immediate: at most n vector memory operations outstanding
-constexpr int vm_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 
 }  // namespace
 
-// ---------------------------------------------------------------------------
-// X (K x N floats, ldb) into operand fragments: block (step s, column block
-// b) holds, for each half step h and part p, 64 lanes of 16 bytes, lane l the
-// values of column 32 b + l % 32 at reduction indices 32 s + 16 h + 8 (l / 32)
-// .. + 7; zero past K and N.  Column blocks of one pass (cwb blocks, the last
-// pass what remains) lie together: pass, step, block.  Memory-bound (4 bytes
-// in, 4 out per value); one wave per (block, half step).
-__device__ __attribute__((always_inline)) inline void xsplit_body(const float* __restrict__ B, int64_t ldb, int K, int N,
-                                                                  float xs, int steps, int nblk, int cwb,
-                                                                  u32x4* __restrict__ out, int bid) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t t = (int64_t)bid * 4 + wave;  // (step, block, half step), half step fastest
-  const int h = (int)(t & 1);
-  const int64_t sb = t >> 1;
-  const int s = (int)(sb / nblk), b = (int)(sb % nblk);
-  if (s >= steps) return;
-  const int n = 32 * b + (lane & 31), k0 = kBK * s + 16 * h + 8 * (lane >> 5);
-  float x[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) x[j] = (n < N && k0 + j < K) ? B[(int64_t)(k0 + j) * ldb + n] : 0.f;
-  u32x4 hi, lo;
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    uint32_t a, c;
-    split2(x[2 * p], x[2 * p + 1], xs, a, c);
-    hi[p] = a;
-    lo[p] = c;
-  }
-  const int pass = b / cwb, first = pass * cwb;
-  const int width = nblk - first < cwb ? nblk - first : cwb;
-  u32x4* o = out + ((int64_t)steps * first + (int64_t)s * width + (b - first)) * 256 + h * 128 + lane;
-  o[0] = hi;
-  o[64] = lo;
-}
-
-__global__ __launch_bounds__(256) void xsplit_kernel(const float* __restrict__ B, int64_t ldb, int K, int N, float xs,
-                                                     int steps, int nblk, int cwb, u32x4* __restrict__ out) {
-  xsplit_body(B, ldb, K, N, xs, steps, nblk, cwb, out, blockIdx.x);
-}
-
-struct XsplitArgs {
-  const float* B;
-  u32x4* out;
-  int64_t ldb;
-  int K, N, steps, nblk, cwb;
-  float xs;
-};
-
-__global__ __launch_bounds__(256) void xsplit_grouped(const XsplitArgs* __restrict__ a, const int* __restrict__ start,
-                                                      int count) {
-  const int p = group_find(start, count, blockIdx.x);
-  const XsplitArgs x = a[p];
-  xsplit_body(device_ptr(x.B), x.ldb, x.K, x.N, x.xs, x.steps, x.nblk, x.cwb, device_ptr(x.out),
-              (int)blockIdx.x - start[p]);
-}
-
-void xsplit_grouped_launch(const void* args, const int* start, int count, unsigned blocks, hipStream_t s) {
-  hipLaunchKernelGGL(xsplit_grouped, dim3(blocks), dim3(256), 0, s, (const XsplitArgs*)args, start, count);
-}
-
-size_t gemm32_split_bytes(int64_t K, int N) { return (size_t)round_up(K, kBK) * round_up(N, 32) * 4; }
-
-void launch_xsplit(const GemmArgs<float>& g, int cw, hipStream_t s) {
-  const int steps = (int)ceil_div(g.K, kBK), nblk = (int)ceil_div(g.N, 32), cwb = cw / 32;
-  const unsigned blocks = (unsigned)ceil_div((int64_t)steps * nblk * 2, 4);
-  const XsplitArgs x{g.B, (u32x4*)g.xsplit, g.ldb, g.K, g.N, steps, nblk, cwb, g.xscale};
-  if (!record_launch(&xsplit_grouped_launch, x, blocks))
-    hipLaunchKernelGGL(xsplit_kernel, dim3(blocks), dim3(256), 0, s, x.B, x.ldb, x.K, x.N, x.xs, steps, nblk, cwb, x.out);
-}
-
-// ---------------------------------------------------------------------------
-// One workgroup's share: tile `logical` = split * mtiles + slab.  Xf: the
-// fragments of this column pass; B, ldb: its values, for the float32 path.
-template <int NB, bool TRANS, int WAVES>
+// One workgroup's share: tile `logical` = split * mtiles + slab.
+// Lane l of a wave holds operand row (A) or column (X) l % 32; its reduction
+// indices of half step h (16 of a step's 32) are 16 h + 8 (j / 4) + 4 (l / 32)
+// + j % 4, j = 0..7: any assignment serves as long as both operands share it,
+// and this one lets a lane load A in runs of four.
+template <int NB, bool TRANS, int WAVES, bool BLOCKED>
 __device__ __attribute__((always_inline)) inline void gemm32_body(
-    const float* __restrict__ A, int64_t lda, const u32x4* __restrict__ Xf, const float* __restrict__ B, int64_t ldb,
-    float* __restrict__ C, int64_t ldc, int64_t cslice, int M, int N, int K, int kchunk, int mtiles, int nst, float xs,
-    int logical) {
-  constexpr int BM = 32 * WAVES;
-  constexpr int NLOADS = 4 * NB;              // 1 KB wave loads per X tile
-  constexpr int LB = (NLOADS + WAVES - 1) / WAVES;  // per wave (the last ones of a wave may repeat a load)
-  constexpr int AH = TRANS ? 8 : 2;           // loads per half step of A
-  // LDS ring of X tiles; with 8 waves (one workgroup per CU) a tile is
-  // requested two steps before its use, with 4 (two workgroups) one
-  constexpr int kStages = WAVES == 8 ? 4 : 3;
-  __shared__ __attribute__((aligned(1024))) u32x4 Bs[kStages][NB * 256];
+    const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb, float* __restrict__ C,
+    int64_t ldc, int64_t cslice, int M, int N, int K, int kchunk, int mtiles, int nst, int logical) {
+  constexpr int BM = 32 * WAVES, BN = 32 * NB, THREADS = 64 * WAVES;
+  constexpr int UNITS = 4 * BN;                           // (column, half step, lane half): 8 values of X each
+  constexpr int UPT = (UNITS + THREADS - 1) / THREADS;
+  __shared__ u32x4 Bs[2][NB * 2 * 3 * 64];                // [block][half step][part][lane]
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -181,264 +118,198 @@ __device__ __attribute__((always_inline)) inline void gemm32_body(
   const int m0 = mt * BM + wave * 32;
   const int kbeg = split * kchunk;
   const int kend = min(K, kbeg + kchunk);
-  // a split that is no whole number of steps takes its short step first
-  const int nsteps = kbeg < kend ? (kend - kbeg + kBK - 1) / kBK : 0;
-  const int nshort = nsteps > 0 ? kend - kbeg - (nsteps - 1) * kBK : 0;  // 1 .. 32
-  const bool ragged = nshort != kBK;
-  // the i-th step taken (past the end, the last: such loads are not used)
-  auto step_id = [&](int i) {
-    i = min(i, nsteps - 1);
-    return ragged ? (i == 0 ? nsteps - 1 : i - 1) : i;
-  };
 
-  // Operand row of lane l: l % 32; its reduction indices in half step h:
-  // 16 h + 8 (l / 32) .. + 7.  NN loads rows l % 16 and 16 + l % 16, four
-  // values at 4 (l / 16) each (64 consecutive bytes of a row per load), and a
-  // half-row swap between the two puts every value in its place.  Rows past M
-  // are read from row M - 1 and not stored.
+  // rows past M are read from row M - 1 and not stored
   const int arow = min(m0 + lc, M - 1);
-  const float* p0;
-  const float* p1;
-  if constexpr (TRANS) {
-    p0 = A + (int64_t)(kbeg + 8 * g) * lda + arow;
-    p1 = p0;
-  } else {
-    p0 = A + (int64_t)min(m0 + (lane & 15), M - 1) * lda + kbeg + 4 * (lane >> 4);
-    p1 = A + (int64_t)min(m0 + 16 + (lane & 15), M - 1) * lda + kbeg + 4 * (lane >> 4);
-  }
-  // A split that is one short step has no whole step to load ahead (loads are
-  // issued all the same): they go to the first bytes of X's fragments instead.
-  const float *q0 = p0, *q1 = p1;
-  int64_t ldq = lda;
-  if (ragged && nsteps == 1) {
-    q0 = q1 = (const float*)Xf;
-    ldq = 0;
-  }
-  float raw[2][2][8];  // loaded values: [parity of the step][half step]
-  auto load_a = [&](auto Pc, auto Hc, int i) {
-    constexpr int P = decltype(Pc)::value, H = decltype(Hc)::value;
-    const int64_t ko = (int64_t)step_id(i) * kBK + 16 * H;
-    if constexpr (TRANS) {
-      const float* p = q0 + ko * ldq;
+  const float* pa = TRANS ? A + (int64_t)(kbeg + 4 * g) * lda + arow : A + (int64_t)arow * lda + kbeg + 4 * g;
+
+  // this thread's units: LDS slot and first reduction index; a unit past the
+  // last one or a column past N reads a valid place, and its values go nowhere
+  // (columns past N are stored as zero)
+  int ul[UPT], uk[UPT];
+  const float* pb[UPT];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) raw[P][H][j] = p[(int64_t)j * ldq];
-    } else {
-      const floatx4u u = *reinterpret_cast<const floatx4u*>(q0 + ko);
-      const floatx4u v = *reinterpret_cast<const floatx4u*>(q1 + ko);
+  for (int u = 0; u < UPT; ++u) {
+    const int e = tid + THREADS * u;
+    const int n = e % BN, hg = (e / BN) & 3, h = hg >> 1, gg = hg & 1;
+    uk[u] = 16 * h + 4 * gg;
+    ul[u] = ((n >> 5) * 2 + h) * 3 * 64 + gg * 32 + (n & 31);
+    pb[u] = B + (int64_t)(kbeg + uk[u]) * ldb + min(n, N - 1);
+  }
+
+  float araw[2][8], braw[UPT][8];
+  u32x4 ap[2][3];   // this wave's A operands: parts of the two half steps
+  u32x4 bp[UPT][3];  // parts of the units on their way to LDS
+  auto load_a = [&](auto Hc, const float* p) {  // half step H of the step at p
+    constexpr int H = decltype(Hc)::value;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        raw[P][H][e] = u[e];
-        raw[P][H][4 + e] = v[e];
+    for (int i = 0; i < 2; ++i) {
+      if constexpr (TRANS) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) araw[H][4 * i + e] = p[(int64_t)(16 * H + 8 * i + e) * lda];
+      } else {
+        const floatx4u v = *reinterpret_cast<const floatx4u*>(p + 16 * H + 8 * i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) araw[H][4 * i + e] = v[e];
       }
     }
   };
-  // the short first step: zeros from its nshort-th value on (read from the
-  // last one)
-  auto load_short = [&] {
-    const int64_t ko = (int64_t)(nsteps - 1) * kBK;
-    const int c = TRANS ? 8 * g : 4 * (lane >> 4);  // in p0 and p1 already
+  auto load_b = [&](int u) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int j = 0; j < 8; ++j) braw[u][j] = pb[u][(int64_t)(8 * (j >> 2) + (j & 3)) * ldb];
+    pb[u] += (int64_t)kBK * ldb;
+  };
+  // the first step: n <= kBK values, zeros after them (read from the n-th)
+  auto load_first = [&](int n) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int kk = 8 * (i >> 2) + (i & 3), ko = min(kk, n - 1 - 4 * g);
+      const float v = pa[TRANS ? (int64_t)ko * lda : (int64_t)ko];
+      araw[i >> 3][i & 7] = 4 * g + kk < n ? v : 0.f;
+    }
+    pa += TRANS ? (int64_t)n * lda : (int64_t)n;
+#pragma unroll
+    for (int u = 0; u < UPT; ++u) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const int kk = 16 * h + (TRANS ? j : j & 3);
-        const int64_t k = ko + min(kk, nshort - 1 - c);
-        const float v = TRANS || j < 4 ? p0[TRANS ? k * lda : k] : p1[k];
-        raw[0][h][j] = c + kk < nshort ? v : 0.f;
+        const int kk = 8 * (j >> 2) + (j & 3);
+        const float v = pb[u][(int64_t)min(kk, n - 1 - uk[u]) * ldb];
+        braw[u][j] = uk[u] + kk < n ? v : 0.f;
       }
-  };
-  auto issue_x = [&](int i) {  // X tile of step i into its ring stage
-    const u32x4* src = Xf + ((int64_t)(kbeg / kBK + step_id(i)) * NB) * 256;
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)src, 0, NB * 4096, 0x00027000);
-    u32x4* dst = Bs[i % kStages];
-#pragma unroll
-    for (int u = 0; u < LB; ++u) {
-      const int j = min(wave + WAVES * u, NLOADS - 1);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(dst + 64 * j), 16, lane * 16, j * 1024, 0, 0);
+      pb[u] += (int64_t)n * ldb;
     }
   };
+  auto split_a = [&](int h, int p) {  // pair p of half step h
+    uint32_t x[3];
+    split3(araw[h][2 * p], araw[h][2 * p + 1], x);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) ap[h][q][p] = x[q];
+  };
+  auto split_b = [&](int u, int p, int buf) {  // pair p of unit u, stored with its last pair
+    uint32_t x[3];
+    split3(braw[u][2 * p], braw[u][2 * p + 1], x);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) bp[u][q][p] = x[q];
+    if (p == 3 && ((u + 1) * THREADS <= UNITS || tid + THREADS * u < UNITS)) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) Bs[buf][ul[u] + 64 * q] = bp[u][q];
+    }
+  };
+  // every LDS access of the step done; the loads in flight stay so
+  auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
   floatx16 acc[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) acc[nb] = (floatx16)0.0f;
 
-  // The scale of operand row arow: 2^-ea, as the factor `as`; values from
-  // athr on need another.  A row whose largest value so far is m takes the
-  // scale that puts m into [2^7, 2^8).
-  int ea = 0;
-  float as = 1.f, athr = 0.f;
-  u32x4 ap[2][2];  // this wave's A operands: [half step][part]
-  auto set_scale = [&](float m) {
-    ea = max((int)(__float_as_uint(m) >> 23) - 127 - 7, -120);
-    as = pow2(-ea);
-    athr = ea + 15 < 128 ? pow2(ea + 15) : __builtin_inff();
-  };
-  auto place = [&](auto Pc, auto Hc) {  // every value to its lane (see above)
-    constexpr int P = decltype(Pc)::value, H = decltype(Hc)::value;
-    if constexpr (!TRANS) {
+  // One half step: the partial products of each column block, the parts of
+  // the next block read from LDS meanwhile; after each block's MFMAs a share
+  // of the splits that the coming half steps need (the other half's A values
+  // and, for the units of this parity, X values for the other LDS buffer), so
+  // that the vector work runs under the matrix work of the same wave.
+  u32x4 b[2][3];
+  auto fetch = [&](int buf, int t) {
+    const u32x4* bs = Bs[buf] + lane;
+    const int h = t / NB, nb = t % NB;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const u32x2 r = __builtin_bit_cast(
-            u32x2, __builtin_amdgcn_permlane16_swap(__float_as_uint(raw[P][H][e]), __float_as_uint(raw[P][H][4 + e]),
-                                                    false, false));
-        raw[P][H][e] = __uint_as_float(r[0]);
-        raw[P][H][4 + e] = __uint_as_float(r[1]);
+    for (int q = 0; q < 3; ++q) b[t & 1][q] = bs[((nb * 2 + h) * 3 + q) * 64];
+  };
+  // partial product x of half step H, smallest first
+  auto product = [&](auto Hc, int x, int cur, floatx16 c) {
+    const int pA = x == 0 ? 2 : (x == 2 || x == 3) ? 1 : 0;
+    const int pB = x == 1 ? 2 : (x == 2 || x == 4) ? 1 : 0;
+    return mma(ap[decltype(Hc)::value][pA], b[cur][pB], c);
+  };
+  auto splits = [&](auto Hc, int buf, int w0, int w1) {  // pairs w0 .. w1 - 1 of half step H's
+    constexpr int H = decltype(Hc)::value;
+    constexpr int NU = (UPT + 1 - H) / 2;  // units H, H + 2, ...
+#pragma unroll
+    for (int w = w0; w < w1; ++w) {
+      if (w < 4 * NU) {
+        split_b(H + 2 * (w / 4), w % 4, buf ^ 1);
+      } else {
+        split_a(H ^ 1, w - 4 * NU);
       }
     }
   };
-  auto absmax = [&](auto Pc, auto Hc) {
-    constexpr int P = decltype(Pc)::value, H = decltype(Hc)::value;
-    float m = fabsf(raw[P][H][0]);
-#pragma unroll
-    for (int j = 1; j < 8; ++j) m = fmaxf(m, fabsf(raw[P][H][j]));
-    return m;
-  };
-  // Rows with a value too large for their scale take another, and what they
-  // have accumulated and the other half's parts, still to be multiplied,
-  // follow.
-  // (Not for what was loaded past the last step.)
-  auto check_scale = [&](auto Pc, auto Hc, bool used) {
+  floatx16 sums[2];  // BLOCKED: this block's and the last one's sums over a half step
+  auto half_step = [&](auto Hc, int buf) {
     constexpr int H = decltype(Hc)::value;
-    float m = absmax(Pc, Hc);
-    if (__builtin_expect(!__any(used && m >= athr), 1)) return;
-    m = fmaxf(m, __shfl_xor(m, 32));
-    const int eo = ea;
-    if (m >= athr) set_scale(m);
-    const int de = max(eo - ea, -250);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int dr = __shfl(de, 8 * (r >> 2) + 4 * g + (r & 3));
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) acc[nb][r] = ldexpf(acc[nb][r], dr);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    const _Float16 f = (_Float16)ldexpf(1.f, de);
-    const f16x8 fv = {f, f, f, f, f, f, f, f};
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-      ap[H ^ 1][q] = __builtin_bit_cast(u32x4, __builtin_bit_cast(f16x8, ap[H ^ 1][q]) * fv);
-  };
-  auto split_a = [&](auto Pc, auto Hc, int p) {  // pair p
-    constexpr int P = decltype(Pc)::value, H = decltype(Hc)::value;
-    uint32_t x, y;
-    split2(raw[P][H][2 * p], raw[P][H][2 * p + 1], as, x, y);
-    ap[H][0][p] = x;
-    ap[H][1][p] = y;
-  };
-
-  // One half step: the partial products of each column block.  A block's
-  // fragments are read from LDS two blocks ahead, each part into the registers
-  // its last product has just freed (across steps, too: `nx` is the next tile
-  // in the second half step), and the A values (SP, SH) that the next half
-  // step needs are split along the way, so that the vector work runs under the
-  // matrix work.
-  u32x4 b[2][2];
-  auto fetch = [&](const u32x4* bs, int t, int q) { b[t & 1][q] = bs[(t % NB * 4 + t / NB * 2 + q) * 64]; };
-  auto half_step = [&](auto Hc, auto SPc, const u32x4* bs, const u32x4* nx, bool used) {
-    constexpr int H = decltype(Hc)::value;
-    using SHc = std::integral_constant<int, H ^ 1>;
+    constexpr int PAIRS = 4 + 4 * ((UPT + 1 - H) / 2);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       const int t = H * NB + nb, cur = t & 1;
-      // one column block: two blocks ahead would be the next tile already in
-      // the first half step, when it need not be there yet
-      constexpr bool AHEAD = NB > 1 || H == 1;
-      const u32x4* fs = t + 2 < 2 * NB ? bs : nx;
-      const int ft = t + 2 < 2 * NB ? t + 2 : t + 2 - 2 * NB;
-      if constexpr (NB == 1 && H == 1) {
-        fetch(nx, 0, 0);
-        fetch(nx, 0, 1);
-      }
-      acc[nb] = mma(ap[H][1], b[cur][0], acc[nb]);
-      acc[nb] = mma(ap[H][0], b[cur][0], acc[nb]);
+      if (t + 1 < 2 * NB) fetch(buf, t + 1);
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (AHEAD) fetch(fs, ft, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      acc[nb] = mma(ap[H][0], b[cur][1], acc[nb]);
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (AHEAD) fetch(fs, ft, 1);
-      if (nb == 0) {
-        place(SPc, SHc{});
-        check_scale(SPc, SHc{}, used);
-      }
+      const int w0 = nb * PAIRS / NB, w1 = (nb + 1) * PAIRS / NB;
+      if constexpr (BLOCKED) {
+        floatx16& sum = sums[cur];
+        sum = (floatx16)0.0f;
 #pragma unroll
-      for (int w = nb * 4 / NB; w < (nb + 1) * 4 / NB; ++w) split_a(SPc, SHc{}, w);
-      __builtin_amdgcn_sched_barrier(0);
+        for (int x = 0; x < 6; ++x) {
+          sum = product(Hc, x, cur, sum);
+          if (t > 0) {
+#pragma unroll
+            for (int r = x * 16 / 6; r < (x + 1) * 16 / 6; ++r) acc[(t + NB - 1) % NB][r] += sums[cur ^ 1][r];
+          }
+          splits(Hc, buf, w0 + x * (w1 - w0) / 6, w0 + (x + 1) * (w1 - w0) / 6);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        // (opaque: the additions stay here, or every sum of the step is kept)
+        if (t > 0) asm volatile("" : "+v"(acc[(t + NB - 1) % NB]));
+      } else {
+#pragma unroll
+        for (int x = 0; x < 6; ++x) acc[nb] = product(Hc, x, cur, acc[nb]);
+        splits(Hc, buf, w0, w1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if constexpr (BLOCKED && H == 1) {
+      acc[NB - 1] += sums[1];
+      asm volatile("" : "+v"(acc[NB - 1]));
     }
   };
-  using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
+  using H0 = std::integral_constant<int, 0>;
+  using H1 = std::integral_constant<int, 1>;
 
-  // Step i of parity P.  At its start raw holds (or awaits) half step 1 of
-  // step i, step i + 1 and half step 0 of step i + 2, and the ring tile i and
-  // (awaited) the kStages - 2 after it.
-  auto step = [&](auto Pc, int i) {
-    constexpr int P = decltype(Pc)::value;
-    using Qc = std::integral_constant<int, P ^ 1>;
-    const u32x4* bs = Bs[i % kStages] + lane;
-    const u32x4* nx = Bs[(i + 1) % kStages] + lane;
-    half_step(I0{}, Pc, bs, nx, true);
-    load_a(Pc, I1{}, i + 2);
-    // This wave's loads of tile i + 1 are done once at most the loads issued
-    // after it are pending: at least 3 half steps of A and, if there is one,
-    // tile i + 2 (8 waves), or 2 half steps of A.  (A's loads are issued in
-    // every step, so that they can be counted.)
-    if (WAVES == 8 && i + 2 < nsteps) __builtin_amdgcn_s_waitcnt(vm_imm(3 * AH + LB));
-    else __builtin_amdgcn_s_waitcnt(vm_imm(WAVES == 8 ? 3 * AH : 2 * AH));
-    // Every wave's part of tile i + 1 is in, and every wave has consumed tile
-    // i - 1, whose stage is filled again (a plain barrier: the loads in flight
-    // stay so).
-    asm volatile("s_barrier" ::: "memory");
-    if (i + kStages - 1 < nsteps) issue_x(i + kStages - 1);
-    half_step(I1{}, Qc{}, bs, nx, i + 1 < nsteps);
-    load_a(Qc{}, I0{}, i + 3);
-  };
-
+  // a split that is no whole number of steps takes the short one first
+  const int nsteps = kbeg < kend ? (kend - kbeg + kBK - 1) / kBK : 0;
+  const int64_t astep = TRANS ? (int64_t)kBK * lda : (int64_t)kBK;
   if (nsteps > 0) {
-    if (ragged) {
-      load_short();
-    } else {
-      load_a(I0{}, I0{}, 0);
-      load_a(I0{}, I1{}, 0);
+    load_first(kend - kbeg - (nsteps - 1) * kBK);
+#pragma unroll
+    for (int u = 0; u < UPT; ++u)
+#pragma unroll
+      for (int p = 0; p < 4; ++p) split_b(u, p, 0);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) split_a(0, p);
+    if (nsteps > 1) {
+#pragma unroll
+      for (int u = 0; u < UPT; ++u) load_b(u);
+      load_a(H0{}, pa);
     }
-    issue_x(0);
-    load_a(I1{}, I0{}, 1);
-    load_a(I1{}, I1{}, 1);
-    if (nsteps > 1) issue_x(1);
-    if (kStages > 3 && nsteps > 2) issue_x(2);
-    {  // the first scales, from the whole first step
-      place(I0{}, I0{});
-      place(I0{}, I1{});
-      const float m = fmaxf(absmax(I0{}, I0{}), absmax(I0{}, I1{}));
-      place(I0{}, I1{});  // (its own inverse: step 0 places half step 1 again)
-      set_scale(fmaxf(m, __shfl_xor(m, 32)));
-    }
+    barrier();
+    int buf = 0;
+    for (int s = 0; s < nsteps; ++s) {
+      // here: Bs[buf] and ap[0] hold step s, araw[1] its other half; braw and
+      // araw[0] hold (or await) step s + 1, where pa points (in the last step
+      // they are left-overs, split into places that are not read again)
+      fetch(buf, 0);
+      half_step(H0{}, buf);
+      if (s + 2 < nsteps) {
 #pragma unroll
-    for (int p = 0; p < 4; ++p) split_a(I0{}, I0{}, p);
-    // tile 0 (and whatever else has been requested so far)
-    __builtin_amdgcn_s_waitcnt(vm_imm(0));
-    asm volatile("s_barrier" ::: "memory");
-    load_a(I0{}, I0{}, 2);
+        for (int u = 0; u < UPT; u += 2) load_b(u);
+      }
+      if (s + 1 < nsteps) load_a(H1{}, pa);
+      half_step(H1{}, buf);
+      if (s + 2 < nsteps) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int q = 0; q < 2; ++q) fetch(Bs[0] + lane, t, q);
-    int i = 0;
-    for (; i + 1 < nsteps; i += 2) {
-      step(I0{}, i);
-      step(I1{}, i + 1);
-    }
-    if (i < nsteps) step(I0{}, i);
-  }
-
-  {  // undo the scales
-    const int ex = 127 - (int)(__float_as_uint(xs) >> 23);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int er = __shfl(ea, 8 * (r >> 2) + 4 * g + (r & 3)) + ex;
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) acc[nb][r] = ldexpf(acc[nb][r], er);
-      __builtin_amdgcn_sched_barrier(0);
+        for (int u = 1; u < UPT; u += 2) load_b(u);
+        pa += astep;
+        load_a(H0{}, pa);
+      }
+      barrier();
+      buf ^= 1;
     }
   }
 
@@ -448,22 +319,30 @@ __device__ __attribute__((always_inline)) inline void gemm32_body(
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const float v = fabsf(acc[nb][r]);
-      bad |= !(v < __builtin_inff()) || (v < 0x1p-96f && v != 0.f);
+      bad |= !(fabsf(acc[nb][r]) < __builtin_inff());
+      acc[nb][r] *= 1.f / (kLift * kLift);
     }
   if (__any(bad)) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[nb] = (floatx16)0.0f;
-    for (int k0 = kbeg; k0 < kend; k0 += 2) {
-      const int k = k0 + g;
-      const bool kin = k < kend;
-      const float a = kin ? A[TRANS ? (int64_t)k * lda + arow : (int64_t)arow * lda + k] : 0.f;
+    constexpr int kRun = 4;  // pairs of reduction indices loaded together
+    for (int k0 = kbeg; k0 < kend; k0 += 2 * kRun) {
+      float a[kRun], x[kRun][NB];
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const int n = nb * 32 + lc;
-        const float x = (kin && n < N) ? B[(int64_t)k * ldb + n] : 0.f;
-        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, x, acc[nb], 0, 0, 0);
+      for (int i = 0; i < kRun; ++i) {
+        const int k = k0 + 2 * i + g;
+        const bool kin = k < kend;
+        a[i] = kin ? A[TRANS ? (int64_t)k * lda + arow : (int64_t)arow * lda + k] : 0.f;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          const int n = nb * 32 + lc;
+          x[i][nb] = (kin && n < N) ? B[(int64_t)k * ldb + n] : 0.f;
+        }
       }
+#pragma unroll
+      for (int i = 0; i < kRun; ++i)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], x[i][nb], acc[nb], 0, 0, 0);
     }
   }
 
@@ -479,81 +358,82 @@ __device__ __attribute__((always_inline)) inline void gemm32_body(
   }
 }
 
-template <int NB, bool TRANS, int WAVES>
+template <int NB, bool TRANS, int WAVES, bool BLOCKED>
 __global__ __launch_bounds__(64 * WAVES, 2) void gemm32_kernel(const float* __restrict__ A, int64_t lda,
-                                                               const u32x4* __restrict__ Xf,
                                                                const float* __restrict__ B, int64_t ldb,
                                                                float* __restrict__ C, int64_t ldc, int64_t cslice,
-                                                               int M, int N, int K, int kchunk, int mtiles, int nst,
-                                                               float xs) {
-  gemm32_body<NB, TRANS, WAVES>(A, lda, Xf, B, ldb, C, ldc, cslice, M, N, K, kchunk, mtiles, nst, xs,
+                                                               int M, int N, int K, int kchunk, int mtiles, int nst) {
+  gemm32_body<NB, TRANS, WAVES, BLOCKED>(A, lda, B, ldb, C, ldc, cslice, M, N, K, kchunk, mtiles, nst,
                                 xcd_remap(blockIdx.x, gridDim.x));
 }
 
 struct Gemm32Args {
   const float* A;
-  const u32x4* Xf;
   const float* B;
   float* C;
   int64_t lda, ldb, ldc, cslice;
   int M, N, K, kchunk, mtiles, nst;
-  float xs;
 };
 
-template <int NB, bool TRANS, int WAVES>
+template <int NB, bool TRANS, int WAVES, bool BLOCKED>
 __global__ __launch_bounds__(64 * WAVES, 2) void gemm32_grouped(const Gemm32Args* __restrict__ a,
                                                                 const int* __restrict__ start, int count) {
   const int p = group_find(start, count, blockIdx.x);
   const Gemm32Args x = a[p];
-  gemm32_body<NB, TRANS, WAVES>(device_ptr(x.A), x.lda, device_ptr(x.Xf), device_ptr(x.B), x.ldb, device_ptr(x.C),
-                                x.ldc, x.cslice, x.M, x.N, x.K, x.kchunk, x.mtiles, x.nst, x.xs,
-                                (int)blockIdx.x - start[p]);
+  gemm32_body<NB, TRANS, WAVES, BLOCKED>(device_ptr(x.A), x.lda, device_ptr(x.B), x.ldb, device_ptr(x.C), x.ldc, x.cslice, x.M,
+                                x.N, x.K, x.kchunk, x.mtiles, x.nst, (int)blockIdx.x - start[p]);
 }
 
-template <int NB, bool TRANS, int WAVES>
+template <int NB, bool TRANS, int WAVES, bool BLOCKED>
 void gemm32_grouped_launch(const void* args, const int* start, int count, unsigned blocks, hipStream_t s) {
-  hipLaunchKernelGGL((gemm32_grouped<NB, TRANS, WAVES>), dim3(blocks), dim3(64 * WAVES), 0, s, (const Gemm32Args*)args,
+  hipLaunchKernelGGL((gemm32_grouped<NB, TRANS, WAVES, BLOCKED>), dim3(blocks), dim3(64 * WAVES), 0, s, (const Gemm32Args*)args,
                      start, count);
 }
 
-template <int NB, bool TRANS, int WAVES>
+template <int NB, bool TRANS, int WAVES, bool BLOCKED>
 static void launch_nb32(const Gemm32Args& x, int grid, hipStream_t s) {
-  if (!record_launch(&gemm32_grouped_launch<NB, TRANS, WAVES>, x, (unsigned)grid))
-    hipLaunchKernelGGL((gemm32_kernel<NB, TRANS, WAVES>), dim3((unsigned)grid), dim3(64 * WAVES), 0, s, x.A, x.lda,
-                       x.Xf, x.B, x.ldb, x.C, x.ldc, x.cslice, x.M, x.N, x.K, x.kchunk, x.mtiles, x.nst, x.xs);
+  if (!record_launch(&gemm32_grouped_launch<NB, TRANS, WAVES, BLOCKED>, x, (unsigned)grid))
+    hipLaunchKernelGGL((gemm32_kernel<NB, TRANS, WAVES, BLOCKED>), dim3((unsigned)grid), dim3(64 * WAVES), 0, s, x.A,
+                       x.lda, x.B, x.ldb, x.C, x.ldc, x.cslice, x.M, x.N, x.K, x.kchunk, x.mtiles, x.nst);
 }
 
-template <bool TRANS, int WAVES>
+template <bool TRANS, int WAVES, bool BLOCKED>
 static void dispatch_nb32(const Gemm32Args& x, int grid, hipStream_t s) {
   switch ((int)ceil_div(x.N, 32)) {
-    case 1: launch_nb32<1, TRANS, WAVES>(x, grid, s); break;
-    case 2: launch_nb32<2, TRANS, WAVES>(x, grid, s); break;
-    case 3: launch_nb32<3, TRANS, WAVES>(x, grid, s); break;
-    case 4: launch_nb32<4, TRANS, WAVES>(x, grid, s); break;
-    case 5: launch_nb32<5, TRANS, WAVES>(x, grid, s); break;
-    case 6: launch_nb32<6, TRANS, WAVES>(x, grid, s); break;
-    case 7: launch_nb32<7, TRANS, WAVES>(x, grid, s); break;
-    case 8: launch_nb32<8, TRANS, WAVES>(x, grid, s); break;
-    default: launch_nb32<9, TRANS, WAVES>(x, grid, s); break;
+    case 1: launch_nb32<1, TRANS, WAVES, BLOCKED>(x, grid, s); break;
+    case 2: launch_nb32<2, TRANS, WAVES, BLOCKED>(x, grid, s); break;
+    case 3: launch_nb32<3, TRANS, WAVES, BLOCKED>(x, grid, s); break;
+    case 4: launch_nb32<4, TRANS, WAVES, BLOCKED>(x, grid, s); break;
+    case 5: launch_nb32<5, TRANS, WAVES, BLOCKED>(x, grid, s); break;
+    case 6: launch_nb32<6, TRANS, WAVES, BLOCKED>(x, grid, s); break;
+    case 7: launch_nb32<7, TRANS, WAVES, BLOCKED>(x, grid, s); break;
+    case 8:
+      if constexpr (!(BLOCKED && WAVES == 8)) launch_nb32<8, TRANS, WAVES, BLOCKED>(x, grid, s);
+      break;
+    default:  // (at most gemm32_max_cols)
+      if constexpr (!(BLOCKED && WAVES == 8)) launch_nb32<9, TRANS, WAVES, BLOCKED>(x, grid, s);
   }
 }
 
-// One column pass from column c0 (g.B and g.N are the pass's own).
-void launch_gemm32_tiles(const GemmArgs<float>& g, int c0, int grid, float* C, int64_t ldc, int64_t cslice, int nst,
-                         hipStream_t s) {
-  if (!g.xsplit) {
-    launch_gemm32_any(g, grid, C, ldc, cslice, nst, s);
-    return;
-  }
-  const u32x4* Xf = (const u32x4*)g.xsplit + ceil_div(g.K, kBK) * (c0 / 32) * 256;
-  const Gemm32Args x{g.A, Xf, g.B, C, g.lda, g.ldb, ldc, cslice, g.M, g.N, g.K, g.kchunk, g.mtiles, nst, g.xscale};
-  if (g.mb == 4) {
-    if (g.trans) dispatch_nb32<true, 8>(x, grid, s);
-    else dispatch_nb32<false, 8>(x, grid, s);
+template <bool BLOCKED>
+static void dispatch_tile32(const Gemm32Args& x, int mb, int trans, int grid, hipStream_t s) {
+  if (mb == 4) {
+    if (trans) dispatch_nb32<true, 8, BLOCKED>(x, grid, s);
+    else dispatch_nb32<false, 8, BLOCKED>(x, grid, s);
   } else {
-    if (g.trans) dispatch_nb32<true, 4>(x, grid, s);
-    else dispatch_nb32<false, 4>(x, grid, s);
+    if (trans) dispatch_nb32<true, 4, BLOCKED>(x, grid, s);
+    else dispatch_nb32<false, 4, BLOCKED>(x, grid, s);
   }
+}
+
+int gemm32_max_cols(const GemmArgs<float>& g) { return g.blocked && g.mb == 4 ? 224 : 288; }
+
+// One column pass (g.B and g.N are the pass's own).
+void launch_gemm32_tiles(const GemmArgs<float>& g, int grid, float* C, int64_t ldc, int64_t cslice, int nst,
+                         hipStream_t s) {
+  const Gemm32Args x{g.A, g.B, C, g.lda, g.ldb, ldc, cslice, g.M, g.N, g.K, g.kchunk, g.mtiles, nst};
+  if (g.blocked) dispatch_tile32<true>(x, g.mb, g.trans, grid, s);
+  else dispatch_tile32<false>(x, g.mb, g.trans, grid, s);
 }
 
 }  // namespace rqlp

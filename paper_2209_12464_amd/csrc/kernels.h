@@ -26,15 +26,11 @@ struct GemmArgs {
   int trans;       // 0: Y = A B, 1: Y = A^T B
   int mtiles;      // ceil(M / gemm_block_rows(mb))
   int nsplit;      // split-K count
-  int kchunk;      // reduction length per split (multiple of 16)
+  int kchunk;      // reduction length per split: whole steps of 16 (double) or 32 (float)
   bool avec;       // A rows 16-byte aligned: vector loads
   bool bvec;       // X rows padded to the tile width with zeros: vector loads
-  int mb = 2;      // row tile: 16 mb rows per wave, 64 mb per workgroup (4: float only)
-  // float: X's values times the power of two xscale lie in float16's range
-  // (save for stray ones), and xsplit (gemm32_split_bytes, 16-byte aligned)
-  // takes their parts; null if X may hold anything
-  float xscale = 0.f;
-  void* xsplit = nullptr;
+  int mb = 2;      // row tile: 64 mb rows per workgroup (4: float only)
+  bool blocked = true;  // float: sums of 16 reduction indices by themselves (k_gemm32.hip)
 };
 // Rows of one workgroup's slab for row-tile parameter mb (128 or 256).
 template <typename T> int gemm_block_rows(int mb);
@@ -46,16 +42,11 @@ template <typename T>
 hipError_t launch_gemm(GemmArgs<T> g, T* Y, int64_t ldy, int nst, T* P, hipStream_t s,
                        hipEvent_t ev0, hipEvent_t ev1);
 
-// The float32 form's main kernel over one column pass from column c0: float16
-// parts from g.xsplit (k_gemm32.hip), or bfloat16 parts made on the way where
-// there is none (k_gemm32x.hip).
-void launch_gemm32_tiles(const GemmArgs<float>& g, int c0, int grid, float* C, int64_t ldc, int64_t cslice, int nst,
+// The float32 form's main kernel over one column pass (k_gemm32.hip), and the most
+// columns of one.
+int gemm32_max_cols(const GemmArgs<float>& g);
+void launch_gemm32_tiles(const GemmArgs<float>& g, int grid, float* C, int64_t ldc, int64_t cslice, int nst,
                          hipStream_t s);
-void launch_gemm32_any(const GemmArgs<float>& g, int grid, float* C, int64_t ldc, int64_t cslice, int nst,
-                       hipStream_t s);
-// g.xsplit = the parts of X, for column passes of cw columns.
-void launch_xsplit(const GemmArgs<float>& g, int cw, hipStream_t s);
-size_t gemm32_split_bytes(int64_t K, int N);
 
 // Y (M x nst, ldy) = sum over s of P[s] (M x nst slabs, ld nst), fixed order.
 hipError_t launch_splitk_reduce_f32(const float* P, int nsplit, int M, int nst, float* Y, int64_t ldy,

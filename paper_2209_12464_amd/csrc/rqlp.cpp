@@ -145,20 +145,25 @@ template <typename T> constexpr int kGemmStep = sizeof(T) == 4 ? 32 : 16;
 // Row tile and split-K count of a float32 product.
 // Up to 48 row tiles of 128 rows (M <= 6144) or for short reductions (K <
 // 1024): 128-row tiles, split to about one 4-wave workgroup per CU (4000 x
-// 4000 x 160: 37.0 us with 8 splits of 128 rows, 38.2 with 12 of 256; 6000 x
-// 3000 x 110: 36.3 / 36.8; 2700 x 2700 x 180: 30.9 / 34.4; 10000 x 300 x 40:
-// 15.1 / 18.0).  Otherwise 256-row tiles, whose X traffic is half, with the
-// split count that fills whole rounds of 256 workgroups best (8000 x 8000 x
-// 210: 111.5 us with 8 splits of 256 rows, 121.6 with 4 of 128; 20000 x 15000
-// x 224: 424 / 534).  Reductions up to 448 are not split: the reduction kernel
-// costs more than it saves (600 x 400 x 30: 14.8 / 16.1 us with 1 / 2 splits;
-// 1000 x 600 x 50: 20.4 / 16.1 with 1 / 3).
-void plan_gemm32(int M, int K, int* mb, int* nsplit) {
+// 4000 x 160: 45.9 us with 8 splits of 128 rows, 46.1 with 16 of 256; 6000 x
+// 3000 x 110: 41.8 / 43.4; 2700 x 2700 x 270: 47.2 / 57.5; 10000 x 300 x 40:
+// 15.7 / 20.1), or two where a workgroup's LDS and registers leave room for
+// the other and its part is long enough to pay for the larger reduction (6000
+// x 6000 x 60: 50.3 / 45.0 us with 5 / 10 splits, 4374 x 5904 x 22: 33.3 /
+// 30.3 with 7 / 14; 6000 x 3000 x 110, parts of 300: 41.8 / 44.1 with 5 / 10).
+// Otherwise 256-row tiles, whose X traffic is half, with the split count that
+// fills whole rounds of 256 workgroups best (8000 x 8000 x 210: 163 us with 8
+// splits of 256 rows, 182 with 4 of 128; 20000 x 15000 x 224: 717 / 845).
+// Reductions up to 448 are not split: the reduction kernel costs what it saves
+// (600 x 400 x 30: 13.8 / 13.5 us with 1 / 2 splits; 1000 x 600 x 50: 23.0 /
+// 15.0 with 1 / 3).
+void plan_gemm32(int M, int N, int K, int* mb, int* nsplit) {
   const int64_t cap = splitk_cap(M, K), mt2 = ceil_div(M, 128), mt4 = ceil_div(M, 256);
   int64_t ns = 1;
   if (mt2 <= 48 || K < 1024) {
     *mb = 2;
     if (K > 448) ns = std::min<int64_t>(cap, std::max<int64_t>(1, 256 / mt2));
+    if (N <= 128 && 512 / mt2 > ns && K >= 400 * (512 / mt2)) ns = std::min<int64_t>(cap, 512 / mt2);
   } else {
     *mb = 4;
     double best = 0.0;
@@ -186,7 +191,7 @@ GemmArgs<T> plan_gemm(int trans, const T* A, int64_t lda, const T* B, int64_t ld
   g.trans = trans;
   g.mb = 2;
   if constexpr (sizeof(T) == 4) {
-    plan_gemm32(M, K, &g.mb, &g.nsplit);
+    plan_gemm32(M, N, K, &g.mb, &g.nsplit);
     g.mtiles = (int)ceil_div(M, gemm_block_rows<T>(g.mb));
     g.kchunk = (int)round_up(ceil_div(std::max(K, 1), g.nsplit), kGemmStep<T>);
     g.nsplit = (int)ceil_div(std::max(K, 1), g.kchunk);
@@ -256,10 +261,7 @@ Layout layout(int64_t m, int64_t n, int d, bool sparse, int64_t nnz, bool bf16 =
   L.om = put((size_t)n * dp * sizeof(T));
   L.yb = put((size_t)mx * dp * sizeof(T));
   L.qi = put((size_t)m * dp * sizeof(T));
-  // also takes the parts of a float32 product's right-hand factor (4 bytes per
-  // value, the reduction dimension rounded up to 32), when no first-pass basis
-  // is held
-  L.q1 = put((size_t)std::max<int64_t>(mx, 16) * dp * sizeof(double));
+  L.q1 = put((size_t)mx * dp * sizeof(double));
   size_t pe = 0;
   if (!sparse) pe = std::max(gemm_partial_elems<T>((int)m, (int)n, dp), gemm_partial_elems<T>((int)n, (int)m, dp));
   if (!sparse)  // the paper orientation's P = P-bar P-tilde (reduction over d)
@@ -397,15 +399,9 @@ rqlp_status cholqr2(rqlp_ctx* c, const T* Y, int64_t ldy, int64_t rows, int d, c
   return RQLP_OK;
 }
 
-// Powers of two that bring the right-hand factors of a float32 product into
-// float16's range: a Gaussian test matrix (|z| <= sqrt(-2 log 2^-53) = 8.6) and
-// a basis (columns of norm 1, or within a few percent after one CholeskyQR
-// pass).  A value beyond the range costs time, not accuracy (k_gemm32.hip).
-constexpr float kScaleGaussian = 0x1p12f, kScaleBasis = 0x1p14f;
-
 template <typename T>
 rqlp_status gemm(rqlp_ctx* c, int trans, const T* A, int64_t lda, int64_t m, int64_t n, const T* X,
-                 int64_t ldx, int d, T* Y, int64_t ldy, int nst, T* P, hipStream_t s, bool padded_x, float xscale, void* xsplit) {
+                 int64_t ldx, int d, T* Y, int64_t ldy, int nst, T* P, hipStream_t s, bool padded_x, bool blocked = true) {
   // trans = 0: Y (m x nst) = A X (K = n); trans = 1: Y (n x nst) = A^T X (K = m)
   const int M = (int)(trans ? n : m), K = (int)(trans ? m : n);
   GemmArgs<T> g = plan_gemm<T>(trans, A, lda, X, ldx, M, d, K);
@@ -417,8 +413,7 @@ rqlp_status gemm(rqlp_ctx* c, int trans, const T* A, int64_t lda, int64_t m, int
   // internal operands have ld = dp and zero padding columns: vector loads
   const int vec = 16 / (int)sizeof(T);
   g.bvec = padded_x && ldx == gemm_block_cols<T>(d) && ldx % vec == 0 && (((uintptr_t)X & 15) == 0);
-  g.xscale = xscale;
-  g.xsplit = xsplit;
+  g.blocked = blocked;
   EvPair t = timer(c, trans ? RQLP_KT_GEMM_TN : RQLP_KT_GEMM_NN);
   HIP_TRY(launch_gemm<T>(g, Y, ldy, nst, P, s, t.a, t.b));
   return RQLP_OK;
@@ -461,7 +456,7 @@ rqlp_status run_method(rqlp_ctx* c, char* base, const Layout& Lo, int64_t m, int
   if (c->reset_info) HIP_TRY(launch_info_reset(c->info, s));
   // Omega (n x d, ld dp), then Y = A Omega and Q = orth(Y)
   HIP_TRY(launch_gaussian<T>(seed, kSketchKey1, n, d, om, dp, s));
-  if ((st = mulA(om, yb, kScaleGaussian)) != RQLP_OK) return st;
+  if ((st = mulA(om, yb)) != RQLP_OK) return st;
   // the bases that only feed the next product of the power iteration take
   // one CholeskyQR pass (see cholqr2); the returned Q and the final QR two
   int oi = 1;
@@ -470,16 +465,16 @@ rqlp_status run_method(rqlp_ctx* c, char* base, const Layout& Lo, int64_t m, int
     return st;
   for (int it = 1; it <= q; ++it) {
     // W = orth(A^T Q) (stored in the Omega buffer), Q = orth(A W)
-    if ((st = mulAt(qi, yb, kScaleBasis)) != RQLP_OK) return st;
+    if ((st = mulAt(qi, yb)) != RQLP_OK) return st;
     if ((st = cholqr2<T>(c, yb, dp, n, d, b, om, dp, dp, nullptr, 0, 0, seed, oi++, s, lowp2, true)) != RQLP_OK)
       return st;
-    if ((st = mulA(om, yb, kScaleBasis)) != RQLP_OK) return st;
+    if ((st = mulA(om, yb)) != RQLP_OK) return st;
     if ((st = cholqr2<T>(c, yb, dp, m, d, b, qi, dp, dp, it == q ? Q : nullptr, d, d, seed, oi++, s, lowp2,
                          it < q)) != RQLP_OK)
       return st;
   }
   // B^T = A^T Q; [V, R] = qr(B^T); L = R^T
-  if ((st = mulAt(qi, yb, kScaleBasis)) != RQLP_OK) return st;
+  if ((st = mulAt(qi, yb)) != RQLP_OK) return st;
   if ((st = cholqr2<T>(c, yb, dp, n, d, b, V, d, d, nullptr, 0, 0, seed, oi++, s, lowp2)) != RQLP_OK) return st;
   HIP_TRY(launch_form_l<T>(b.r2, b.r1, b.flags, d, dp, Lout, ldl > 0 ? ldl : d, s));
   return RQLP_OK;
@@ -513,7 +508,7 @@ rqlp_status run_method_paper(rqlp_ctx* c, char* base, const Layout& Lo, int64_t 
   // [P-tilde, R-tilde] = qr(R^T) (the QR after the 2q + 2 of the method); L = R-tilde^T
   if ((st = cholqr2<T>(c, rt, dp, d, d, b, pt, dp, dp, nullptr, 0, 0, seed, 2 * q + 3, s)) != RQLP_OK) return st;
   HIP_TRY(launch_form_l<T>(b.r2, b.r1, b.flags, d, dp, Lout, d, s));
-  return gemm<T>(c, 0, pb, dp, n, d, pt, dp, d, P, d, d, part, s, true, kScaleBasis, b.q1);
+  return gemm<T>(c, 0, pb, dp, n, d, pt, dp, d, P, d, d, part, s, true);
 }
 
 template <typename T>
@@ -525,14 +520,8 @@ rqlp_status decompose_dense(rqlp_ctx* c, const T* A, int64_t m, int64_t n, int64
   rqlp_status st = get_workspace(c, ws, ws_bytes, Lo.total, &base);
   if (st != RQLP_OK) return st;
   T* part = (T*)(base + Lo.part);
-  // (the first-pass basis is not held while a product runs: its buffer takes
-  // the parts of X)
-  auto mulA = [&](const T* X, T* Y, float xs) {
-    return gemm<T>(c, 0, A, lda, m, n, X, dp, d, Y, dp, dp, part, s, true, xs, base + Lo.q1);
-  };
-  auto mulAt = [&](const T* X, T* Y, float xs) {
-    return gemm<T>(c, 1, A, lda, m, n, X, dp, d, Y, dp, dp, part, s, true, xs, base + Lo.q1);
-  };
+  auto mulA = [&](const T* X, T* Y) { return gemm<T>(c, 0, A, lda, m, n, X, dp, d, Y, dp, dp, part, s, true); };
+  auto mulAt = [&](const T* X, T* Y) { return gemm<T>(c, 1, A, lda, m, n, X, dp, d, Y, dp, dp, part, s, true); };
   return run_method<T>(c, base, Lo, m, n, k, p, q, seed, Q, L, V, s, mulA, mulAt);
 }
 
@@ -545,14 +534,8 @@ rqlp_status decompose_paper(rqlp_ctx* c, const T* A, int64_t m, int64_t n, int64
   rqlp_status st = get_workspace(c, ws, ws_bytes, Lo.total, &base);
   if (st != RQLP_OK) return st;
   T* part = (T*)(base + Lo.part);
-  // (the first-pass basis is not held while a product runs: its buffer takes
-  // the parts of X)
-  auto mulA = [&](const T* X, T* Y, float xs) {
-    return gemm<T>(c, 0, A, lda, m, n, X, dp, d, Y, dp, dp, part, s, true, xs, base + Lo.q1);
-  };
-  auto mulAt = [&](const T* X, T* Y, float xs) {
-    return gemm<T>(c, 1, A, lda, m, n, X, dp, d, Y, dp, dp, part, s, true, xs, base + Lo.q1);
-  };
+  auto mulA = [&](const T* X, T* Y) { return gemm<T>(c, 0, A, lda, m, n, X, dp, d, Y, dp, dp, part, s, true); };
+  auto mulAt = [&](const T* X, T* Y) { return gemm<T>(c, 1, A, lda, m, n, X, dp, d, Y, dp, dp, part, s, true); };
   return run_method_paper<T>(c, base, Lo, m, n, k, p, q, seed, Q, L, P, s, mulA, mulAt);
 }
 
@@ -576,13 +559,13 @@ rqlp_status decompose_dense_bf16(rqlp_ctx* c, const float* A, int64_t m, int64_t
   uint16_t* xt = (uint16_t*)(base + Lo.xt);
   const int64_t ldn = bf16_ld(n), ldm = bf16_ld(m);
   HIP_TRY(launch_cvt_bf16(A, lda, m, n, ab, ldn, at, ldm, s));
-  auto mulA = [&](const float* X, float* Y, float) -> rqlp_status {  // Y (m x dp) = A X, X n x dp
+  auto mulA = [&](const float* X, float* Y) -> rqlp_status {  // Y (m x dp) = A X, X n x dp
     HIP_TRY(launch_cvt_bf16_t(X, dp, n, dp, xt, ldn, s));
     EvPair t = timer(c, RQLP_KT_GEMM_NN);
     HIP_TRY(launch_gemm_bf16(ab, ldn, xt, ldn, (int)m, dp, (int)ldn, Y, dp, dp, part, s, t.a, t.b));
     return RQLP_OK;
   };
-  auto mulAt = [&](const float* X, float* Y, float) -> rqlp_status {  // Y (n x dp) = A^T X, X m x dp
+  auto mulAt = [&](const float* X, float* Y) -> rqlp_status {  // Y (n x dp) = A^T X, X m x dp
     HIP_TRY(launch_cvt_bf16_t(X, dp, m, dp, xt, ldm, s));
     EvPair t = timer(c, RQLP_KT_GEMM_TN);
     HIP_TRY(launch_gemm_bf16(at, ldm, xt, ldm, (int)n, dp, (int)ldm, Y, dp, dp, part, s, t.a, t.b));
@@ -606,12 +589,12 @@ rqlp_status decompose_csr(rqlp_ctx* c, const int32_t* rowptr, const int32_t* col
   int32_t* ct = (int32_t*)(base + Lo.csr_ct);
   T* vt = (T*)(base + Lo.csr_vt);
   HIP_TRY(launch_csr_transpose<T>(rowptr, colidx, vals, m, n, nnz, rt, ct, vt, base + Lo.csr_scr, s));
-  auto mulA = [&](const T* X, T* Y, float) -> rqlp_status {
+  auto mulA = [&](const T* X, T* Y) -> rqlp_status {
     EvPair t = timer(c, RQLP_KT_SPMM);
     HIP_TRY(launch_spmm<T>(rowptr, colidx, vals, m, X, dp, d, Y, dp, dp, s, t.a, t.b));
     return RQLP_OK;
   };
-  auto mulAt = [&](const T* X, T* Y, float) -> rqlp_status {
+  auto mulAt = [&](const T* X, T* Y) -> rqlp_status {
     EvPair t = timer(c, RQLP_KT_SPMM);
     HIP_TRY(launch_spmm<T>(rt, ct, vt, n, X, dp, d, Y, dp, dp, s, t.a, t.b));
     return RQLP_OK;
@@ -929,7 +912,7 @@ SvdLayout svd_layout(int64_t m, int64_t n, int d, rqlp_precision prec) {
 // L = U-bar diag(S) V-bar^T, then U = Q U-bar and W = V V-bar.
 template <typename T>
 rqlp_status svd_like(rqlp_ctx* c, const SvdLayout& Ly, char* b, int64_t m, int64_t n, int d, T* U, T* S, T* W,
-                     void* xsplit, hipStream_t s) {
+                     hipStream_t s) {
   T* Q = (T*)(b + Ly.q);
   T* L = (T*)(b + Ly.l);
   T* V = (T*)(b + Ly.v);
@@ -937,9 +920,9 @@ rqlp_status svd_like(rqlp_ctx* c, const SvdLayout& Ly, char* b, int64_t m, int64
   T* Vb = (T*)(b + Ly.vb);
   T* part = (T*)(b + Ly.part);
   HIP_TRY(launch_svd_small<T>(L, d, d, Ub, d, S, Vb, d, b + Ly.svd, c->info, s));
-  rqlp_status st = gemm<T>(c, 0, Q, d, m, d, Ub, d, d, U, d, d, part, s, false, kScaleBasis, xsplit);
+  rqlp_status st = gemm<T>(c, 0, Q, d, m, d, Ub, d, d, U, d, d, part, s, false);
   if (st != RQLP_OK) return st;
-  return gemm<T>(c, 0, V, d, n, d, Vb, d, d, W, d, d, part, s, false, kScaleBasis, xsplit);
+  return gemm<T>(c, 0, V, d, n, d, Vb, d, d, W, d, d, part, s, false);
 }
 
 // ---- autotuner --------------------------------------------------------------
@@ -950,12 +933,10 @@ rqlp_status svd_like(rqlp_ctx* c, const SvdLayout& Ly, char* b, int64_t m, int64
 // keep the fastest in the context's plan table.  Synchronizes.
 template <typename T>
 rqlp_status autotune_product(rqlp_ctx* c, int trans, const T* A, int64_t lda, int64_t m, int64_t n, int d, T* X,
-                             T* Y, T* P, void* xsplit, hipStream_t s, int* best_out) {
+                             T* Y, T* P, hipStream_t s, int* best_out) {
   const int dp = padded_d(d);
   const int M = (int)(trans ? n : m), K = (int)(trans ? m : n);
   GemmArgs<T> g0 = plan_gemm<T>(trans, A, lda, X, dp, M, d, K);
-  g0.xscale = kScaleBasis;
-  g0.xsplit = sizeof(T) == 4 ? xsplit : nullptr;
   const int vec = 16 / (int)sizeof(T);
   g0.bvec = dp == gemm_block_cols<T>(d) && dp % vec == 0 && (((uintptr_t)X & 15) == 0);
   const int cap = splitk_cap(M, K);
@@ -1013,16 +994,14 @@ rqlp_status autotune_dense(rqlp_ctx* c, const T* A, int64_t m, int64_t n, int64_
   const size_t pe = std::max(gemm_partial_elems<T>((int)m, (int)n, dp), gemm_partial_elems<T>((int)n, (int)m, dp));
   const size_t xb = align256((size_t)std::max(m, n) * dp * sizeof(T));
   char* base = nullptr;
-  rqlp_status st = get_workspace(
-      c, nullptr, 0, 2 * xb + align256(pe * sizeof(T)) + gemm32_split_bytes(std::max(m, n), d) + 256, &base);
+  rqlp_status st = get_workspace(c, nullptr, 0, 2 * xb + align256(pe * sizeof(T)) + 256, &base);
   if (st != RQLP_OK) return st;
   T* X = (T*)base;
   T* Y = (T*)(base + xb);
   T* P = (T*)(base + 2 * xb);
-  void* xsplit = base + 2 * xb + align256(pe * sizeof(T));
   HIP_TRY(hipMemsetAsync(X, 0, xb, s));  // operand values do not change the timing
-  if ((st = autotune_product<T>(c, 0, A, lda, m, n, d, X, Y, P, xsplit, s, best_nn)) != RQLP_OK) return st;
-  return autotune_product<T>(c, 1, A, lda, m, n, d, X, Y, P, xsplit, s, best_tn);
+  if ((st = autotune_product<T>(c, 0, A, lda, m, n, d, X, Y, P, s, best_nn)) != RQLP_OK) return st;
+  return autotune_product<T>(c, 1, A, lda, m, n, d, X, Y, P, s, best_tn);
 }
 
 }  // namespace
@@ -1386,7 +1365,7 @@ rqlp_status rqlp_decompose_svd(rqlp_ctx* c, const void* A, int64_t m, int64_t n,
     if ((st = decompose_dense<double>(c, (const double*)A, m, n, lda, k, p, q, seed, (double*)(sb + Ly.q),
                                       (double*)(sb + Ly.l), (double*)(sb + Ly.v), base, dec, s)) != RQLP_OK)
       return st;
-    return svd_like<double>(c, Ly, sb, m, n, d, (double*)U, (double*)S, (double*)W, nullptr, s);
+    return svd_like<double>(c, Ly, sb, m, n, d, (double*)U, (double*)S, (double*)W, s);
   }
   if (prec == RQLP_BF16_REFINED)
     st = decompose_dense_bf16(c, (const float*)A, m, n, lda, k, p, q, seed, (float*)(sb + Ly.q), (float*)(sb + Ly.l),
@@ -1395,8 +1374,7 @@ rqlp_status rqlp_decompose_svd(rqlp_ctx* c, const void* A, int64_t m, int64_t n,
     st = decompose_dense<float>(c, (const float*)A, m, n, lda, k, p, q, seed, (float*)(sb + Ly.q),
                                 (float*)(sb + Ly.l), (float*)(sb + Ly.v), base, dec, s);
   if (st != RQLP_OK) return st;
-  return svd_like<float>(c, Ly, sb, m, n, d, (float*)U, (float*)S, (float*)W,
-                         base + layout<float>(m, n, d, false, 0, prec == RQLP_BF16_REFINED).q1, s);
+  return svd_like<float>(c, Ly, sb, m, n, d, (float*)U, (float*)S, (float*)W, s);
 }
 
 size_t rqlp_workspace_size_paper(int64_t m, int64_t n, int k, int p, int q, rqlp_precision prec) {
@@ -1521,9 +1499,9 @@ rqlp_status rqlp_gemm(rqlp_ctx* c, int trans, const void* A, int64_t m, int64_t 
   // the partial buffer is laid out with row length d here (nst = d)
   if (prec == RQLP_FP64)
     return gemm<double>(c, trans, (const double*)A, lda, m, n, (const double*)X, ldx, d, (double*)Y, ldy, d,
-                        (double*)base, s, false, 0.f, nullptr);
+                        (double*)base, s, false);
   return gemm<float>(c, trans, (const float*)A, lda, m, n, (const float*)X, ldx, d, (float*)Y, ldy, d,
-                     (float*)base, s, false, 0.f, nullptr);
+                     (float*)base, s, false, false);
 }
 
 size_t rqlp_orth_workspace_size(int64_t rows, int d, rqlp_precision prec) {

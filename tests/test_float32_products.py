@@ -111,3 +111,56 @@ def test_gemm_range_ends(gpu_lib, trans):
     assert np.array_equal(np.isnan(Y), np.isnan(ref)) and np.array_equal(np.isinf(Y), np.isinf(ref))
     assert np.array_equal(np.sign(Y[np.isinf(ref)]), np.sign(ref[np.isinf(ref)]))
     assert np.all(np.abs(Y[fine] - ref[fine]) <= 2 * k * U * bound[fine])
+
+
+def _jump(rng, k, n):
+    """Columns of k = 64 values whose second-last 16 are a hundred times and whose
+    last 16 hold one value 2^25 times the first: every fourth one; the others
+    Gaussian and as large."""
+    A = rng.standard_normal((k, n)) * 2.0 ** 25
+    for j in range(0, n, 4):
+        sign = rng.choice([-1.0, 1.0], k)
+        A[:, j] = rng.uniform(1.0, 1.9, k) * sign
+        A[32:48, j] = rng.uniform(200.0, 250.0, 16) * sign[32:48]
+        A[48 + rng.integers(16), j] = 2.0 ** 25
+    return A
+
+
+def _large_row(rng, k, n):
+    """One row 2^19 times the others: the bases' other columns are as small there."""
+    A = rng.standard_normal((k, n))
+    A[37] *= 2.0 ** 19
+    return A
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("form", [_jump, _large_row])
+@pytest.mark.parametrize("trans", [False, True])
+def test_gemm_uneven_values(gpu_lib, form, trans):
+    """Every output is as accurate as a float32 dot product, whatever the size of
+    the other values of its row and column: within 64 roundings of sum |a x|, for X
+    Gaussian and as uneven as A."""
+    announce("float32 gemm uneven", form.__name__, trans)
+    rng = np.random.default_rng(11)
+    A = form(rng, 64, 200).T.astype(np.float32)
+    for X in (rng.standard_normal((64, 48)), 1.0 / form(rng, 64, 48)):
+        X = X.astype(np.float32)
+        ref, bound = _ref(A, X, False)
+        Y = _gemm(gpu_lib, np.ascontiguousarray(A.T) if trans else np.ascontiguousarray(A), X, trans)
+        assert np.all(np.abs(Y - ref) <= 64 * U * bound)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("form", [_jump, _large_row])
+def test_decompose_uneven_values(gpu_lib, form):
+    """The last product of a decomposition, L V^T = Q^T A, entry by entry: within
+    64 + 4 roundings of sum |q a| (the product and Q's own) and 8 of sum |l v|."""
+    import torch
+    announce("float32 decompose uneven", form.__name__)
+    A = form(np.random.default_rng(12), 64, 200).astype(np.float32)
+    out = gpu_lib.decompose(to_dev(A), 40, 8 if form is _jump else 0, 0, seed=3)
+    torch.cuda.synchronize()
+    Q, L, V = (x.cpu().numpy().astype(np.float64) for x in out)
+    A64 = A.astype(np.float64)
+    err = np.abs(L @ V.T - Q.T @ A64)
+    assert np.all(err <= U * (68 * np.abs(Q).T @ np.abs(A64) + 8 * np.abs(L) @ np.abs(V).T))
