@@ -112,8 +112,8 @@ __device__ __forceinline__ void row_fma1(double& s0, double& w0, double ts, doub
 // column.  Rows below lose S[i][P] / d times row P, and row P goes to LDS as it is
 // (its factor 1 / sqrt(d) is left to those who read it).  d, the pivot, and
 // r = 1 / d are in every lane and become the next ones, taken on a chain of their
-// own (a reciprocal and one FMA from pivot to pivot) whose operations stand
-// between the rows' and hide behind them.  dv and rv collect d and -r, lane c
+// own (a reciprocal, a product and one FMA from pivot to pivot) whose operations
+// stand between the rows' and hide behind them.  dv and rv collect d and -r, lane c
 // those of column c.  CHECK: a pivot at or below thr is a dependent column, it
 // eliminates nothing, and its row is zero outside the diagonal tile (`panel`
 // lanes); a branch at every pivot costs half as much again as the elimination, so
@@ -138,7 +138,7 @@ __device__ __forceinline__ void pivot_step(double (&S)[kTile], double (&W)[kTile
   if constexpr (P + 1 < kTile) {
     const double next = row_bcast<P + 1>(S[P + 1]), b = row_bcast<P>(S[P + 1]);
     const double ts = -r * S[P], tw = -r * W[P];
-    d = fma(-(b * b), r, next);
+    d = fma(-(b * r), b, next);  // (b b leaves the range at columns of norm 1e77 and 1e-81)
     double y = 0.0, e = 0.0;
     auto rows = [&]<int I>(std::integral_constant<int, I>) {  // rows P + 1 + 2 I, P + 2 + 2 I
       constexpr int i = P + 1 + 2 * I;

@@ -189,6 +189,26 @@ def test_orth_rank_deficient_completes_basis(gpu_lib, dtype):
     assert np.all(R[dep, :] == 0.0)
 
 
+@pytest.mark.parametrize("scale", [1e-140, 1e-100, 1e-82, 1e-60, 1e60, 1e78, 1e100, 1e140])
+@pytest.mark.parametrize("d", [40, 300])
+def test_orth_scales(gpu_lib, d, scale):
+    """Columns whose squared norms are far from 1, their squares out of float64's
+    range, and that are nearly parallel, so that the first pivots decide: the factors
+    of the scaled matrix, R to a few hundred roundings of cond(Y) = 1e3 (the
+    factorizations of both take the same steps)."""
+    announce("orth scales", d, scale)
+    rng = np.random.default_rng(d)
+    Y = rng.standard_normal((700, d)) + 30.0 * rng.standard_normal((700, 1))
+    ctx = gpu_lib.default_context(0)
+    Q, R = (to_np(t) for t in gpu_lib.orth(to_dev(Y * scale), want_r=True, ctx=ctx))
+    assert ctx.info()["completed_cols"] == 0
+    assert np.linalg.norm(Q.T @ Q - np.eye(d)) <= 1e-11
+    assert np.linalg.norm(Q @ (R / scale) - Y) <= 1e-11 * np.linalg.norm(Y)
+    ref = np.linalg.qr(Y)[1]
+    ref *= np.sign(np.diag(ref))[:, None]
+    assert np.linalg.norm(R / scale - ref) <= 1e-10 * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("d", [16, 17, 33, 160, 161, 224, 225, 256])
 @pytest.mark.parametrize("ndep", [0, 1, 3])
 def test_orth_tile_edges(gpu_lib, d, ndep):
