@@ -71,6 +71,21 @@ def test_svd_small_block_edges(gpu_lib, d, scale):
     assert np.abs(Ug.T @ Ug - np.eye(d)).max() <= tol * d
 
 
+@pytest.mark.parametrize("d", [210, 320])
+def test_svd_small_values_accuracy(gpu_lib, d):
+    """The singular values of a factor with a slow spectrum, whose columns take part
+    in some ten rotations with every other: within 1.5 d roundings in norm (a
+    rotation's rounding is a factor of a column's norm, and must not be one-sided)."""
+    announce("svd_small values", d)
+    rng = np.random.default_rng(d)
+    u, v = (np.linalg.qr(rng.standard_normal((d, d)))[0] for _ in range(2))
+    M = (u * np.arange(1, d + 1) ** -0.5) @ v.T
+    M = np.ascontiguousarray(np.linalg.qr(M.T @ np.linalg.qr(M @ rng.standard_normal((d, d)))[0])[1].T)
+    _, Sg, _ = (to_np(x) for x in gpu_lib.svd_small(to_dev(M)))
+    So = np.linalg.svd(M, compute_uv=False)
+    assert np.linalg.norm(Sg - So) <= 1.5 * d * 2.0 ** -53 * np.linalg.norm(So)
+
+
 @pytest.mark.parametrize("d", [15, 16, 40])
 @pytest.mark.parametrize("value", [1.0, 0.1])
 def test_svd_small_rank_one(gpu_lib, d, value):
