@@ -999,7 +999,9 @@ rqlp_status autotune_dense(rqlp_ctx* c, const T* A, int64_t m, int64_t n, int64_
   T* X = (T*)base;
   T* Y = (T*)(base + xb);
   T* P = (T*)(base + 2 * xb);
-  HIP_TRY(hipMemsetAsync(X, 0, xb, s));  // operand values do not change the timing
+  // values as a decomposition's first product has them: large float32 products are
+  // bound by the power they draw, and zeros draw less
+  HIP_TRY(launch_gaussian<T>(1, kSketchKey1, std::max(m, n), d, X, dp, s));
   if ((st = autotune_product<T>(c, 0, A, lda, m, n, d, X, Y, P, s, best_nn)) != RQLP_OK) return st;
   return autotune_product<T>(c, 1, A, lda, m, n, d, X, Y, P, s, best_tn);
 }
