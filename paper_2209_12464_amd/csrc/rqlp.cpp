@@ -126,11 +126,12 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 int padded_d(int d) { return (int)round_up(d, 32); }
 
-int env_int(const char* name, int dflt) {
+bool env_set(const char* name) {
   const char* v = getenv(name);
-  if (!v || !*v) return dflt;
-  return atoi(v);
+  return v && *v;
 }
+
+int env_int(const char* name, int dflt) { return env_set(name) ? atoi(getenv(name)) : dflt; }
 
 // Largest split-K count a plan may take (default or autotuned): enough
 // splits for about four workgroups per CU, none shorter than 256.
@@ -190,7 +191,8 @@ GemmArgs<T> plan_gemm(int trans, const T* A, int64_t lda, const T* B, int64_t ld
   g.K = K;
   g.trans = trans;
   g.mb = 2;
-  if constexpr (sizeof(T) == 4) {
+  // (either variable asks for the rule below, in float32 too)
+  if (sizeof(T) == 4 && !env_set("RQLP_GEMM_TARGET_WGS") && !env_set("RQLP_GEMM_MIN_KCHUNK")) {
     plan_gemm32(M, N, K, &g.mb, &g.nsplit);
     g.mtiles = (int)ceil_div(M, gemm_block_rows<T>(g.mb));
     g.kchunk = (int)round_up(ceil_div(std::max(K, 1), g.nsplit), kGemmStep<T>);
@@ -210,7 +212,7 @@ GemmArgs<T> plan_gemm(int trans, const T* A, int64_t lda, const T* B, int64_t ld
   int64_t ns = target / g.mtiles;
   ns = std::min<int64_t>(ns, std::max<int64_t>(1, ceil_div(K, kmin)));
   ns = std::max<int64_t>(1, ns);
-  g.kchunk = (int)round_up(ceil_div(std::max(K, 1), ns), 16);
+  g.kchunk = (int)round_up(ceil_div(std::max(K, 1), ns), kGemmStep<T>);
   g.nsplit = (int)ceil_div(std::max(K, 1), g.kchunk);
   const int vec = 16 / (int)sizeof(T);
   g.avec = (lda % vec == 0) && (((uintptr_t)A & 15) == 0);

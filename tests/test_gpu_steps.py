@@ -72,6 +72,28 @@ def test_gemm_matches_matmul(gpu_lib, trans, m, n, d, dtype):
     assert np.all(np.abs(Y - ref) <= 2 * K * u * bound + 1e-300)
 
 
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_gemm_plan_environment(gpu_lib, monkeypatch, dtype):
+    """RQLP_GEMM_TARGET_WGS and RQLP_GEMM_MIN_KCHUNK set the split of the reduction,
+    and so the summation order, of products of both types."""
+    announce("gemm plan environment", dtype)
+    rng = np.random.default_rng(2)
+    A, X = to_dev(rng.standard_normal((500, 3000)), dtype), to_dev(rng.standard_normal((3000, 40)), dtype)
+    default = gpu_lib.gemm(A, X)
+    ref, bound = to_np(A) @ to_np(X), np.abs(to_np(A)) @ np.abs(to_np(X))
+    u = 2.0 ** -53 if dtype == torch.float64 else 2.0 ** -24
+    for name, value in (("RQLP_GEMM_TARGET_WGS", "1"), ("RQLP_GEMM_MIN_KCHUNK", "1500")):
+        with monkeypatch.context() as env:
+            env.setenv(name, value)
+            Y = gpu_lib.gemm(A, X)
+            torch.cuda.synchronize()
+        assert not torch.equal(Y, default), name
+        assert np.all(np.abs(to_np(Y) - ref) <= 2 * 3000 * u * bound)
+    again = gpu_lib.gemm(A, X)
+    torch.cuda.synchronize()
+    assert torch.equal(again, default)
+
+
 def test_gemm_unaligned_leading_dimension(gpu_lib):
     announce("gemm unaligned lda")
     rng = np.random.default_rng(3)
