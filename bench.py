@@ -496,12 +496,10 @@ def copy_calibration(nbytes=1 << 30, reps=5):
 
 def kernel_class(name):
     """Timed kernel class of a profiled kernel name (None if untimed)."""
-    if name.startswith("void rqlp::gemm_kernel<"):
-        trans = name.split("<", 1)[1].split(",")[2].strip()
-        return "gemm_tn" if trans == "true" else "gemm_nn"
-    if name.startswith("void rqlp::gemm32_kernel<"):
-        trans = name.split("<", 1)[1].split(",")[1].strip()
-        return "gemm_tn" if trans == "true" else "gemm_nn"
+    if name.startswith(("void rqlp::gemm_kernel<", "void rqlp::gemm32_kernel<")):
+        # the first truth value among the template arguments: whether A is transposed
+        args = [a.strip() for a in name.split("<", 1)[1].split(">", 1)[0].split(",")]
+        return "gemm_tn" if next(a for a in args if a in ("true", "false")) == "true" else "gemm_nn"
     if "rqlp::spmm_kernel" in name:
         return "spmm"
     return None

@@ -125,3 +125,19 @@ def test_committed_records_match_current_sources():
             assert util is not None and 0.0 < util < 1.0 and 1.5 < clock < 2.5, (workload, k)
             assert bench.load_traffic(workload, k) is not None, (workload, k)
     assert bench.load_traffic("csr100k", "spmm") is not None
+
+
+@pytest.mark.parametrize("name,cls", [
+    ("void rqlp::gemm_kernel<7, false, true, true>(double const*, long)", "gemm_nn"),
+    ("void rqlp::gemm_kernel<7, true, true, true>(double const*, long)", "gemm_tn"),
+    ("void rqlp::gemm_kernel<1, false, false, false>(double const*, long)", "gemm_nn"),
+    ("void rqlp::gemm_kernel<1, true, false, true>(double const*, long)", "gemm_tn"),
+    ("void rqlp::gemm32_kernel<7, false, 8, true>(float const*, long)", "gemm_nn"),
+    ("void rqlp::gemm32_kernel<9, true, 4, false>(float const*, long)", "gemm_tn"),
+    ("void rqlp::spmm_kernel<float, 2>(int const*)", "spmm"),
+    ("void rqlp::chol_kernel<14>(double const*)", None),
+    ("void rqlp::gemm32_grouped<7, true, 4, true>(rqlp::Gemm32Args const*)", None),
+])
+def test_kernel_class_of_profiled_names(name, cls):
+    """The products' direction is read from the kernels' names as they are now."""
+    assert bench.kernel_class(name) == cls
