@@ -164,3 +164,53 @@ def test_decompose_uneven_values(gpu_lib, form):
     A64 = A.astype(np.float64)
     err = np.abs(L @ V.T - Q.T @ A64)
     assert np.all(err <= U * (68 * np.abs(Q).T @ np.abs(A64) + 8 * np.abs(L) @ np.abs(V).T))
+
+
+def _decompose(gpu_lib, A, d, q, seed):
+    import torch
+    out = gpu_lib.decompose(to_dev(A), d, 0, q, seed=seed)
+    torch.cuda.synchronize()
+    return (x.cpu().numpy().astype(np.float64) for x in out)
+
+
+def _check_products(A, Q, L, V, seed):
+    """Both products of a decomposition at q = 0 against 64 bits, each row relative to
+    its own size: Y = A Omega = Q R row by row (a rounding error dY reaches row i as
+    dY_i and as Q_i Q^T dY; Q's own rounding as Q_i R), L V^T = Q^T A entry by entry
+    (see test_decompose_uneven_values)."""
+    from oracle import philox
+    m, n = A.shape
+    A64 = A.astype(np.float64)
+    om = philox.gaussian_matrix(seed, n, L.shape[0]).astype(np.float32).astype(np.float64)
+    Y, bound = A64 @ om, np.abs(A64) @ np.abs(om)
+    err = np.linalg.norm(Y - Q @ (Q.T @ Y), axis=1)
+    own, all_rows = np.linalg.norm(bound, axis=1), np.linalg.norm(bound)
+    assert np.all(err <= U * ((n + 4) * own + np.linalg.norm(Q, axis=1) * ((n + 4) * all_rows + 8 * np.linalg.norm(Y))))
+    err = np.abs(L @ V.T - Q.T @ A64)
+    assert np.all(err <= U * ((m + 4) * np.abs(Q).T @ np.abs(A64) + 8 * np.abs(L) @ np.abs(V).T))
+
+
+# the decompositions' form at the 256-row tile in both directions, with ragged
+# reductions: one column pass and two; nine column blocks at the 128-row tile
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,d", [(6401, 1111, 40), (1111, 6401, 40), (6401, 1111, 224), (1111, 6401, 225),
+                                   (1300, 700, 280), (6145, 1024, 1), (4374, 5904, 22)])
+def test_decompose_row_tiles(gpu_lib, m, n, d):
+    announce("float32 decompose tiles", m, n, d)
+    A = np.random.default_rng(m + d).standard_normal((m, n)).astype(np.float32)
+    _check_products(A, *_decompose(gpu_lib, A, d, 0, 5), 5)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shift", [-60, -30, -18])
+@pytest.mark.parametrize("side", ["rows", "columns"])
+def test_decompose_small_rows(gpu_lib, side, shift):
+    """Rows or columns far smaller than the others, graded ones among them, are as
+    accurate relative to themselves."""
+    announce("float32 decompose small rows", side, shift)
+    A = np.random.default_rng(21).standard_normal((300, 260))
+    scale = np.ones(300 if side == "rows" else 260)
+    scale[:96] = 2.0 ** shift
+    scale[96:144] = 2.0 ** (shift * np.arange(48) / 48)
+    A = (A * scale[:, None] if side == "rows" else A * scale).astype(np.float32)
+    _check_products(A, *_decompose(gpu_lib, A, 40, 0, 6), 6)
