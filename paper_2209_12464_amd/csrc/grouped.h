@@ -62,7 +62,7 @@ inline bool record_launch(GroupedFn fn, const A& a, unsigned blocks) {
 // A pointer that a grouped kernel reads from its argument table, as one into
 // device memory.  The compiler knows that of a kernel's own arguments only: from
 // the table it would make flat accesses, which also count as LDS accesses, so that
-// every wait for LDS waits for memory (a batch of 20 problems 3822 -> 3763 us).
+// every wait for LDS waits for memory (20 serving-sized problems in one call: 1.5 %).
 template <typename T>
 __device__ __forceinline__ T* device_ptr(T* p) {
   return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;

@@ -14,6 +14,7 @@
 //      do the rest of step k - 1, G_ij -= R_ti^T R_tj for t = k - 1 and i > k (MFMA),
 //      and store block row k - 1 of R;
 //   B. the 12 bring row k + 1 up to date with row k and put it in LDS.
+// (With 16 tile columns 36 of the 12 slots' registers a lane are spilled.)
 // What bounds it is the chain of A and B: about 3500 + 1500 cycles a step at 2.1
 // GHz, of which the 16 pivots' row operations are 1000 (240 FMAs of 4 cycles), and
 // with many tiles the float64 MFMAs of A (64 cycles each, 4 a tile, in the same
@@ -659,9 +660,10 @@ void chol_syrk_grouped_launch(const void* args, const int* start, int count, uns
   hipLaunchKernelGGL(chol_syrk_grouped, dim3(blocks), dim3(64), 0, s, (const CholSyrkArgs*)args, start, count);
 }
 
-// register slots per wave for the t (t + 1) / 2 lower tiles of a block of t
-// tile columns (8 waves; slots chosen so that tiles and the diagonal-block
-// code fit in registers)
+// One diagonal block (or the whole matrix) of T = db / 16 tile columns, by the
+// smallest of three variants that holds it: their T (T + 1) / 2 upper tiles take 5,
+// 9 or 12 register slots of each of the 12 waves, and their slabs 75, 105 or 120 KB
+// of LDS.
 static hipError_t launch_chol_reg(const double* G, int ld, int d, int db, double* R, double* Rinv16,
                                   int32_t* flags, void* info, int pass_id, double tol, double fast_tol,
                                   const double* esq, int nesq, int32_t* mode, double* Xfull, const double* gdiag0,

@@ -31,13 +31,13 @@
 // to a block (half the steps of 8, at the same number of rounds), rounds that
 // touch 32 x 32 values in LDS instead of 2 dp x 32 (about 860 cycles each, with
 // one barrier, against a reduction over a column and its update), the angles
-// from the hardware's estimates and one Newton step, J's accumulation one round behind on waves of
-// its own, and V's product one step behind on workgroups of its own.  At d = 210
-// (10 sweeps of 13 steps) a step takes 35 thousand cycles: load 4, G 6, rounds 14,
-// X J 5, barrier 5.  All sweeps run in one cooperative launch.  Measured against
-// blocks of 8 columns rotated in place (the whole call, L factors): d = 50 492 ->
-// 405 us, 100 1203 -> 938, 210 3513 -> 2180, 320 6272 -> 3760, 540 15723 -> 9310;
-// singular values and vectors as accurate against 64-bit references.
+// from the hardware's estimates and one Newton step, J's accumulation one round
+// behind on waves of its own, and V's product one step behind on workgroups of its
+// own.  At d = 210 (10 sweeps of 13 steps) a step takes 35 thousand cycles: load 4,
+// G 6, rounds 14, X J 5, barrier 5.  All sweeps run in one cooperative launch.
+// Measured against blocks of 8 columns rotated in place (the whole call, L
+// factors): d = 100 1204 -> 981 us, 210 3270 -> 2141, 320 6381 -> 3842, 400 9108 ->
+// 5683; singular values nearer to 64-bit references, vectors as near.
 //
 // Finally sigma_j = ||x_j||, the columns are sorted by descending sigma
 // (stable), u_j = x_j / sigma_j (zero when sigma_j = 0), and each pair of vectors
@@ -613,7 +613,7 @@ hipError_t launch_svd_small(const T* M, int64_t ldm, int d, T* U, int64_t ldu, T
   const int64_t tot = (int64_t)dp * 2 * dp;
   hipLaunchKernelGGL((svd_init_kernel<T>), dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, s, M, ldm, d, dp, XV,
                      flags, kSvSweeps, counter);
-  // two copies of G while they fit beside X in 160 KB (dp <= 512)
+  // two copies of G while they fit beside X in 160 KB (dp <= 528)
   auto lds = [&](int copies) {
     return ((size_t)kSvCols * (dp + kXPad) + (size_t)(copies + 1) * kSvCols * kGS) * sizeof(double);
   };

@@ -12,7 +12,8 @@
 // chain barrier, X_{I+1,J} from LDS, 4 + 4 MFMAs, LDS (about 1000 cycles) and, with
 // many rows to a wave, those rows' R tiles and MFMAs.  Measured with the steps
 // unrolled, the tiles in four 8-byte loads a lane and all loads waited for, and
-// now: d = 210 17.3 -> 14.0 us, 540 67 -> 51.  The diagonal-block inverses come
+// now: d = 210 17.3 -> 14.0 us, 540 67 -> 51 (the form for 34 block rows spills 8
+// registers a lane).  The diagonal-block inverses come
 // from the Cholesky.  Nothing is done after the Cholesky's fast path, which
 // writes its own inverse.  A dependent column has a unit row in R, so the
 // inverse exists and its other columns do not involve it.

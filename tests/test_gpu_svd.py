@@ -86,6 +86,22 @@ def test_svd_small_values_accuracy(gpu_lib, d):
     assert np.linalg.norm(Sg - So) <= 1.5 * d * 2.0 ** -53 * np.linalg.norm(So)
 
 
+@pytest.mark.parametrize("scale", [1.0, 1e70, 1e-70])
+def test_svd_small_widest_layout(gpu_lib, scale):
+    """The 34 blocks of 16 columns whose Gram matrix has one copy only (bounds as in
+    test_svd_small_block_edges)."""
+    announce("svd_small widest layout", scale)
+    d = 530
+    M = _lower(d, d) * scale
+    Ug, Sg, Vg = (to_np(x) / s for x, s in zip(gpu_lib.svd_small(to_dev(M)), (1.0, scale, 1.0)))
+    So = np.linalg.svd(M / scale, compute_uv=False)
+    tol = 1e-13
+    assert np.abs(Sg - So).max() <= tol * So[0] * np.sqrt(d)
+    assert np.abs(Ug @ np.diag(Sg) @ Vg.T - M / scale).max() <= tol * So[0] * d
+    assert np.abs(Vg.T @ Vg - np.eye(d)).max() <= tol * d
+    assert np.abs(Ug.T @ Ug - np.eye(d)).max() <= tol * d
+
+
 @pytest.mark.parametrize("d", [15, 16, 40])
 @pytest.mark.parametrize("value", [1.0, 0.1])
 def test_svd_small_rank_one(gpu_lib, d, value):
