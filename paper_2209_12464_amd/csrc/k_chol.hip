@@ -76,46 +76,49 @@ __device__ __forceinline__ double row_bcast(double v) {
   return __longlong_as_double(__builtin_amdgcn_update_dpp((long long)0, b, 0x150 + C, 0xf, 0xf, true));  // row_newbcast
 }
 
-// W_i += S_i[P] tw and then S_i += S_i[P] ts, S_i[P] taken from lane P of each row
-// of 16 lanes by the FMA itself (a move of its own for each S_i[P] makes a chain
-// of two instructions, twice the time: one wave a SIMD has nothing to hide it
-// with).  A value written by a vector instruction can be read across lanes two
-// instructions later: FIRST, at a pivot's first rows, waits for what came before,
-// and for what the compiler does with these rows next.
-#define RQLP_ROW_FMA "row_newbcast:%[p] row_mask:0xf bank_mask:0xf\n\t"
-template <int P, bool FIRST>
-__device__ __forceinline__ void row_fma2(double& s0, double& w0, double& s1, double& w1, double ts, double tw) {
+// W_i += sp[i] tw and S_i += sp[i] ts, sp[i] taken from lane i of each row of 16
+// lanes by the FMA itself (a move of its own for each sp[i] makes a chain of two
+// instructions, twice the time: one wave a SIMD has nothing to hide it with).  A
+// value written by a vector instruction can be read across lanes two instructions
+// later: FIRST, at a pivot's first rows, waits for what came before, and for what
+// the compiler does with these rows next.
+#define RQLP_ROW_FMA(d, t, i) \
+  "v_fmac_f64_dpp %[" d "], %[sp], %[" t "] row_newbcast:%[" i "] row_mask:0xf bank_mask:0xf\n\t"
+#define RQLP_ROW_FMA2                                       \
+  RQLP_ROW_FMA("w0", "tw", "i") RQLP_ROW_FMA("w1", "tw", "j") \
+  RQLP_ROW_FMA("s0", "ts", "i") RQLP_ROW_FMA("s1", "ts", "j")
+template <int I, bool FIRST>
+__device__ __forceinline__ void row_fma2(double sp, double& s0, double& w0, double& s1, double& w1, double ts,
+                                         double tw) {
   if constexpr (FIRST)
-    asm volatile("s_nop 1\n\t"
-                 "v_fmac_f64_dpp %[w0], %[s0], %[tw] " RQLP_ROW_FMA "v_fmac_f64_dpp %[w1], %[s1], %[tw] " RQLP_ROW_FMA
-                 "v_fmac_f64_dpp %[s0], %[s0], %[ts] " RQLP_ROW_FMA "v_fmac_f64_dpp %[s1], %[s1], %[ts] " RQLP_ROW_FMA
-                 "s_nop 1"
-                 : [s0] "+v"(s0), [w0] "+v"(w0), [s1] "+v"(s1), [w1] "+v"(w1)
-                 : [ts] "v"(ts), [tw] "v"(tw), [p] "i"(P));
+    asm volatile("s_nop 1\n\t" RQLP_ROW_FMA2 "s_nop 1"
+                 : [s0] "+&v"(s0), [w0] "+&v"(w0), [s1] "+&v"(s1), [w1] "+&v"(w1)
+                 : [sp] "v"(sp), [ts] "v"(ts), [tw] "v"(tw), [i] "i"(I), [j] "i"(I + 1));
   else
-    asm volatile("v_fmac_f64_dpp %[w0], %[s0], %[tw] " RQLP_ROW_FMA "v_fmac_f64_dpp %[w1], %[s1], %[tw] " RQLP_ROW_FMA
-                 "v_fmac_f64_dpp %[s0], %[s0], %[ts] " RQLP_ROW_FMA "v_fmac_f64_dpp %[s1], %[s1], %[ts] " RQLP_ROW_FMA
-                 : [s0] "+v"(s0), [w0] "+v"(w0), [s1] "+v"(s1), [w1] "+v"(w1)
-                 : [ts] "v"(ts), [tw] "v"(tw), [p] "i"(P));
+    asm volatile(RQLP_ROW_FMA2
+                 : [s0] "+&v"(s0), [w0] "+&v"(w0), [s1] "+&v"(s1), [w1] "+&v"(w1)
+                 : [sp] "v"(sp), [ts] "v"(ts), [tw] "v"(tw), [i] "i"(I), [j] "i"(I + 1));
 }
-template <int P>
-__device__ __forceinline__ void row_fma1(double& s0, double& w0, double ts, double tw) {
-  asm volatile("s_nop 1\n\t"
-               "v_fmac_f64_dpp %[w0], %[s0], %[tw] " RQLP_ROW_FMA "v_fmac_f64_dpp %[s0], %[s0], %[ts] " RQLP_ROW_FMA
-               "s_nop 1"
-               : [s0] "+v"(s0), [w0] "+v"(w0)
-               : [ts] "v"(ts), [tw] "v"(tw), [p] "i"(P));
+template <int I>
+__device__ __forceinline__ void row_fma1(double sp, double& s0, double& w0, double ts, double tw) {
+  asm volatile("s_nop 1\n\t" RQLP_ROW_FMA("w0", "tw", "i") RQLP_ROW_FMA("s0", "ts", "i") "s_nop 1"
+               : [s0] "+&v"(s0), [w0] "+&v"(w0)
+               : [sp] "v"(sp), [ts] "v"(ts), [tw] "v"(tw), [i] "i"(I));
 }
+#undef RQLP_ROW_FMA2
 #undef RQLP_ROW_FMA
 
 // Pivot P of the elimination of a 16-row slab: S[i] holds row i of the diagonal
 // tile (lane c of each row of 16 lanes: column c), W[i] row i of this lane's own
-// column.  Rows below lose S[i][P] / d times row P, and row P goes to LDS as it is
-// (its factor 1 / sqrt(d) is left to those who read it).  d, the pivot, and
-// r = 1 / d are in every lane and become the next ones, taken on a chain of their
-// own (a reciprocal, a product and one FMA from pivot to pivot) whose operations
-// stand between the rows' and hide behind them.  dv and rv collect d and -r, lane c
-// those of column c.  CHECK: a pivot at or below thr is a dependent column, it
+// column.  Rows below lose S[P][i] / d times row P, and row P goes to LDS as it is
+// (its factor 1 / sqrt(d) is left to those who read it).  S[P][i] and not S[i][P],
+// which rounds differently: the identity's columns have to see the very entries that
+// become R, or X R - I is a thousand times as large (1.5e-11 for 1.2e-14 at d = 110),
+// and R of the two passes with it less accurate (at condition 4e5 1.8e-15 for 7e-16,
+// at 3e7 1.9e-13 for 1.1e-15).  What lies below the diagonal is not used.  d, the pivot, and r = 1 / d are in every lane and become the
+// next ones, taken on a chain of their own (a reciprocal, a product and one FMA from
+// pivot to pivot) whose operations stand between the rows' and hide behind them.  dv
+// and rv collect d and -r, lane c those of column c.  CHECK: a pivot at or below thr is a dependent column, it
 // eliminates nothing, and its row is zero outside the diagonal tile (`panel`
 // lanes); a branch at every pivot costs half as much again as the elimination, so
 // it is first done without.
@@ -137,14 +140,14 @@ __device__ __forceinline__ void pivot_step(double (&S)[kTile], double (&W)[kTile
   put_s[P * LD] = S[P];  // (the same from every wave and row of 16 lanes)
   rv = lc == P ? -r : rv;
   if constexpr (P + 1 < kTile) {
-    const double next = row_bcast<P + 1>(S[P + 1]), b = row_bcast<P>(S[P + 1]);
+    const double next = row_bcast<P + 1>(S[P + 1]), b = row_bcast<P + 1>(S[P]);
     const double ts = -r * S[P], tw = -r * W[P];
     d = fma(-(b * r), b, next);  // (b b leaves the range at columns of norm 1e77 and 1e-81)
     double y = 0.0, e = 0.0;
     auto rows = [&]<int I>(std::integral_constant<int, I>) {  // rows P + 1 + 2 I, P + 2 + 2 I
       constexpr int i = P + 1 + 2 * I;
-      if constexpr (i + 1 < kTile) row_fma2<P, I == 0>(S[i], W[i], S[i + 1], W[i + 1], ts, tw);
-      else if constexpr (i < kTile) row_fma1<P>(S[i], W[i], ts, tw);
+      if constexpr (i + 1 < kTile) row_fma2<i, I == 0>(S[P], S[i], W[i], S[i + 1], W[i + 1], ts, tw);
+      else if constexpr (i < kTile) row_fma1<i>(S[P], S[i], W[i], ts, tw);
     };
     // 1 / d as rcp_f64 takes it, an operation after each pair of rows
     y = __builtin_amdgcn_rcp(d);

@@ -211,6 +211,30 @@ def test_orth_rank_deficient_completes_basis(gpu_lib, dtype):
     assert np.all(R[dep, :] == 0.0)
 
 
+@pytest.mark.parametrize("power", [1.0, 1.5, 2.0])
+def test_orth_r_accuracy(gpu_lib, power):
+    """R of matrices with condition numbers from 4e5 to 3e7, against extended
+    precision: within 2 sqrt(d) roundings in norm.  (The second pass makes up for the
+    first pass's Gram matrix only if the first R and its inverse belong together to
+    working accuracy.)"""
+    announce("orth R accuracy", power)
+    m, d = 1500, 110
+    rng = np.random.default_rng(0)
+    Y = rng.standard_normal((m, d)) @ ((np.arange(1, d + 1) ** -power)[:, None] * rng.standard_normal((d, d)))
+    Q, ref = Y.astype(np.longdouble), np.eye(d, dtype=np.longdouble)
+    for _ in range(2):  # Gram-Schmidt, twice
+        N, R = np.zeros_like(Q), np.zeros_like(ref)
+        for j in range(d):
+            R[:j, j] = N[:, :j].T @ Q[:, j]
+            v = Q[:, j] - N[:, :j] @ R[:j, j]
+            R[j, j] = np.sqrt((v * v).sum())
+            N[:, j] = v / R[j, j]
+        Q, ref = N, R @ ref
+    _, R = gpu_lib.orth(to_dev(Y), want_r=True)
+    err = np.linalg.norm((to_np(R) - ref).astype(np.float64)) / np.linalg.norm(ref.astype(np.float64))
+    assert err <= 2 * np.sqrt(d) * 2.0 ** -53
+
+
 @pytest.mark.parametrize("scale", [1e-140, 1e-100, 1e-82, 1e-60, 1e60, 1e78, 1e100, 1e140])
 @pytest.mark.parametrize("d", [40, 300])
 def test_orth_scales(gpu_lib, d, scale):
